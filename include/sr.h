@@ -461,12 +461,15 @@ sr_status sr_launch_config_kernel(const char *kernel /*host*/, int waves_per_cu,
  * blocks of 64 are the dense particles) each unordered pair of dense
  * particles is evaluated once and its opposite term kept as well (Newton's
  * third law on the short-range sum of Sec. 2); the rest is summed from both
- * ends as before.  blocks_per_item: blocks of 64 targets one work item takes
- * (1..256; 0 switches the symmetric tiles off; -1 keeps the value); window:
- * sources per work item, 256 or 512 (-1 keeps).  Larger tiles need fewer
- * partial slots but make longer items.  The partial slots (12 bytes each)
+ * ends as before.  blocks_per_item: most blocks of 64 targets one work item
+ * takes (1..256; 0 switches the symmetric tiles off; -1 keeps the value);
+ * window: sources per window of an item, 256 or 512 (-1 keeps).  Larger items
+ * need fewer partial slots but spread worse; with a balance ratio above 0
+ * (sr_tile_balance) the device cuts items down to a sixteenth of these blocks
+ * where there is little work.  The partial slots (12 bytes each)
  * fill the tail of the workspace: sr_workspace_bytes reserves about 15 per
- * particle, and a larger workspace passed to sr_force / sr_force_vjp lends
+ * particle (up to 47 from 2^19 particles on, at most 805 MB more), and a
+ * larger workspace passed to sr_force / sr_force_vjp lends
  * its whole tail to them.  A problem that needs more (very large cells) runs
  * without symmetric tiles.  Results differ from the one-sided sums only in rounding
  * order; for fixed tiles they are bitwise reproducible.  cur (nullable)
@@ -481,12 +484,15 @@ sr_status sr_tile_config(const char *kernel /*host*/, int blocks_per_item, int w
  * Batch plans tune their own.  cur (nullable) receives the value in effect. */
 sr_status sr_sparse_group(int group, int *cur /*host out*/);
 
-/* Host only.  When the symmetric tiles pay: they run only if their work (tile
- * steps of all items) spread over the persistent grid's waves is at least
- * min_ratio times the longest item, so that a few long items cannot leave
- * most waves idle; the decision is taken on the device after binning, like
- * the pool check.  min_ratio >= 0 (0: whenever the partial slots fit; -1
- * keeps the value); initial value 1, or SR_SYM_BALANCE.  Batch plans do not
+/* Host only.  How well the symmetric tiles have to spread.  Items are as large
+ * as the tile configuration allows while their work (tile steps of all items)
+ * spread over the persistent grid's waves is at least 5 min_ratio times the
+ * longest item, and smaller otherwise, so that a few long items cannot leave
+ * most waves idle; the tiles are off only when the smallest items' work does
+ * not even give four waves per compute unit min_ratio times the longest one.
+ * The decision is taken on the device after binning, like the pool check.
+ * min_ratio >= 0 (0: always the configured items, whenever their partial
+ * slots fit; -1 keeps the value); initial value 1, or SR_SYM_BALANCE.  Batch plans do not
  * apply it: their tuner times the tiles against none, and every mode of a
  * plan takes the same decision.  Results of either path agree to rounding
  * order; cur (nullable) receives the value in effect. */

@@ -132,6 +132,17 @@ void sym_tail(Layout &L, size_t ws_bytes)
     L.sym_pool = L.sym_items + align256((size_t)L.sym_item_cap * 16);
 }
 
+// Partial slots of a layout: 16 per particle, and from 2^19 particles on up to
+// 32 more (at most 2^26, 805 MB) for boxes with a few very large halos: the
+// 2.1 million particle box whose halos reach 55,000 particles a cell needs 31
+// at items of 16 blocks and two windows.  Smaller problems keep to what the
+// fixed workspace of sr_force_static was sized for.
+int64_t sym_slots(int64_t N)
+{
+    const int64_t more = N >= (int64_t(1) << 19) ? std::min<int64_t>(32 * N, int64_t(1) << 26) : 0;
+    return kSymSlotsPerParticle * N + more;
+}
+
 Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_passive, int code_bits)
 {
     Layout L;
@@ -192,7 +203,7 @@ Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_pas
     L.sym_info = take((size_t)NC * 4);
     // the tail: symmetric items and the pool, sized for the default number of
     // slots per particle; a larger workspace lends the tail more (sym_tail)
-    const int64_t cap = std::min<int64_t>((int64_t)kSymSlotsPerParticle * N, kSymMaxSlots);
+    const int64_t cap = std::min<int64_t>(sym_slots(N), kSymMaxSlots);
     L.sym_items = o;
     L.total = o + sym_tail_bytes(cap);
     sym_tail(L, L.total);

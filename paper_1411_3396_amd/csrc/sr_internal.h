@@ -69,17 +69,19 @@ enum HdrWord : int {
     kHdrMagic = 2,          // written by the last binning kernel: bins are ready
     kHdrMassInfo = 3,       // 0 if every mass equals the first one
     kHdrBucketCount = 64,   // [32]
-    kHdrBucketBase = 128,   // [33]
     kHdrBucketCursor = 192, // [32]
     kHdrQueue = 256,        // queue q at kHdrQueue + 32*q (separate 128-byte lines)
     kHdrPairs = 512,        // int64 pair counter (2 words)
-    kHdrSymTotal = 516,     // int64 partial slots the symmetric tiles need (2 words)
     kHdrSymOk = 518,        // 1: symmetric tiles run (their partial slots fit the pool)
     kHdrSymNItems = 519,    // symmetric work items
     kHdrSymWork = 520,      // int64 tile steps of all symmetric items (2 words)
-    kHdrSymMaxItem = 522,   // tile steps of the longest symmetric item
+    kHdrSymK = 522,         // shape of the symmetric items: blocks of 64 targets
+    kHdrSymR = 523,         // and consecutive windows
+    kHdrSymAlloc = 524,     // partial slots given out
+    kHdrSymDone = 525,      // workgroups of the shape decision that are through
+    kHdrSymSlots = 528,     // int64 partial slots per shape [kSymShapes]
     kHdrSymBucketCount = 544,   // [32]
-    kHdrSymBucketBase = 576,    // [33]
+    kHdrSymLongest = 576,       // tile steps of the longest item per shape [kSymShapes]
     kHdrSymBucketCursor = 640,  // [32]
     kHdrSymQueue = 768,     // symmetric queue q at kHdrSymQueue + 32*q
     kHdrWords = 1024
@@ -94,6 +96,7 @@ constexpr int kSymSegs = kSymDirs + kSymNdDirs;  // source segments of a symmetr
 // per cell: target slots, then source slots of its dense particles for the 14
 // directions, then source slots of its non-dense particles for the 27
 constexpr int kSymStride = 1 + kSymDirs + kSymNdDirs;
+constexpr int kSymShapes = 6;       // item shapes tried, coarse to fine
 constexpr int kSymSlotsPerParticle = 16;  // partial-slot pool: this many 12-byte slots per particle
 
 // Byte offsets of every buffer inside a workspace.
@@ -143,11 +146,11 @@ struct DevArgs {
     int n_rows;  // rows of the force output (sum of n_active)
     int targets_per_lane;  // 1 or 2 for cells with more than 64 targets
     int occupancy;         // register-allocation hint of the pair kernels: 0, 6 or 8 waves/SIMD
-    int sym_blocks;        // symmetric tiles: blocks of 64 targets per item (0: symmetric tiles off)
+    int sym_blocks;        // symmetric tiles: most blocks of 64 targets per item (0: symmetric tiles off)
     int sym_window;        // symmetric tiles: sources per item window (256 or 512)
-    int sym_rounds;        // symmetric tiles: consecutive windows per item (1 or 2)
+    int sym_rounds;        // symmetric tiles: most consecutive windows per item (1 or 2)
     int sym_occupancy;     // symmetric tiles: register-allocation hint, 0 or 5 waves/SIMD
-    double sym_balance;    // symmetric tiles run only if their steps per wave reach this many longest items
+    double sym_balance;    // symmetric tiles: how well their items must spread over the waves (0: one fixed shape)
     int sparse_group;      // most targets per item of a cell (or remainder) with fewer than 64: 8, 16, 32 or 64
     int64_t pull_limit;    // most items one wave of a persistent kernel may pull (test hook)
 };

@@ -20,6 +20,8 @@
 //
 // Everything is integer-deterministic or summed in a fixed order: no float
 // atomics, so results are bitwise reproducible run to run.
+#include <algorithm>
+
 #include "sr_internal.h"
 
 namespace sr {
@@ -455,7 +457,8 @@ __global__ __launch_bounds__(256) void k_gather(Acc acc, int N, const int *__res
     bz[b] = v.z;
     const float mi = v.w;
     bm[b] = mi;
-    if (!(mi == packed[0].w)) atomicOr(&hdr[kHdrMassInfo], 1u);  // not every mass equal
+    // not every mass equal (the plain read spares most of the adds to one address)
+    if (!(mi == packed[0].w) && hdr[kHdrMassInfo] == 0) atomicOr(&hdr[kHdrMassInfo], 1u);
     const int li = i - S.part_off;
     const bool act = li < S.n_active;
     out_row[b] = act ? S.out_off + li : -1;
@@ -572,148 +575,6 @@ __device__ __forceinline__ int64_t run_cost(int nt, int64_t src, bool two, int g
     const int lk = nt >= kTargetsPerItem ? 0 : lanes_log2(min(nt, group));
     const int chunk = (two && nt > kTargetsPerItem) ? 2 * kTargetsPerItem : kTargetsPerItem;
     return ((src + (1 << lk) - 1) >> lk) * (chunk / kTargetsPerItem);
-}
-
-// Per home cell: number of items and cost class (floor log2 of the pairs one
-// lane evaluates); counts items per class.  The forward takes the cell's
-// active targets against every source of the 27 cells.  The adjoint also
-// takes its passive targets, as items of their own whose sources are only
-// the active particles of the 27 cells: a pair of two passive particles has
-// u = m_k g_j - m_j g_k = 0, so it adds exactly nothing.
-template <class Acc, bool kActiveOnly>
-__device__ __forceinline__ void items_count_cell(const Acc &acc, int c, int NC,
-                                                 const int *__restrict__ start,
-                                                 const int *__restrict__ nact,
-                                                 uint32_t *__restrict__ info, uint32_t *blk,
-                                                 bool ok, int N, bool two, bool sym, int group)
-{
-    if (c >= NC) return;
-    if (!ok) {
-        info[c] = 0;
-        return;
-    }
-    const int na = nact[c];
-    const int np = kActiveOnly ? 0 : (start[c + 1] - start[c]) - na;
-    if (na < 0 || np < 0 || na + np <= 0 || na + np > N) {
-        info[c] = 0;
-        return;
-    }
-    const SegParams &S = acc.get(acc.seg_of_cell(c));
-    int ix, iy, iz;
-    decode_cell(S, c, ix, iy, iz);
-    int64_t src = 0, src_act = 0, src_nd = 0, src_act_nd = 0;
-    for (int dx = -1; dx <= 1; ++dx) {
-        int jx = ix + dx;
-        if (jx < 0 || jx >= S.nc[0]) {
-            if (!S.periodic) continue;
-            jx = (jx + S.nc[0]) % S.nc[0];
-        }
-        for (int dy = -1; dy <= 1; ++dy) {
-            int jy = iy + dy;
-            if (jy < 0 || jy >= S.nc[1]) {
-                if (!S.periodic) continue;
-                jy = (jy + S.nc[1]) % S.nc[1];
-            }
-            for (int dz = -1; dz <= 1; ++dz) {
-                int jz = iz + dz;
-                if (jz < 0 || jz >= S.nc[2]) {
-                    if (!S.periodic) continue;
-                    jz = (jz + S.nc[2]) % S.nc[2];
-                }
-                const int cc = S.cell_off + (jx * S.nc[1] + jy) * S.nc[2] + jz;
-                src += start[cc + 1] - start[cc];
-                if (np > 0) src_act += nact[cc];
-                if (sym) {
-                    src_nd += start[cc + 1] - start[cc] - dense_count(nact[cc]);
-                    src_act_nd += nact[cc] - dense_count(nact[cc]);
-                }
-            }
-        }
-    }
-    // cost class from the cell's widest item: a group of min(nt, group) targets when sparse.
-    // With symmetric tiles the dense blocks have no item here, and the other
-    // targets take only the non-dense sources (the symmetric tiles give them
-    // the terms of the dense ones)
-    const int dn = sym ? dense_count(na) : 0;
-    const int n_items = cell_items(na - dn, two, group) + cell_items(np, two, group);
-    int64_t cost = sym ? max(run_cost(na - dn, src_nd, two, group), run_cost(np, src_act_nd, two, group))
-                       : max(run_cost(na, src, two, group), run_cost(np, src_act, two, group));
-    if (cost < 1) cost = 1;
-    int cls = 63 - __clzll((unsigned long long)cost);
-    cls = cls > 31 ? 31 : cls;
-    info[c] = ((uint32_t)n_items << 5) | (uint32_t)cls;
-    // per-block class totals, one global atomic per class and block
-    atomicAdd(&blk[cls], (uint32_t)n_items);
-}
-
-template <class Acc, bool kActiveOnly>
-__global__ __launch_bounds__(256) void k_items_count(Acc acc, int NC, const int *__restrict__ start,
-                                                     const int *__restrict__ nact,
-                                                     uint32_t *__restrict__ info, uint32_t *hdr,
-                                                     uint32_t magic, int N, int two, int group)
-{
-    __shared__ uint32_t blk[kClasses];
-    if (threadIdx.x < kClasses) blk[threadIdx.x] = 0;
-    __syncthreads();
-    const bool ok = hdr[kHdrMagic] == magic;
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (!ok && c == 0) atomicOr(&hdr[kHdrFlags], (uint32_t)SR_FLAG_NOT_BINNED);
-    items_count_cell<Acc, kActiveOnly>(acc, c, NC, start, nact, info, blk, ok, N, two != 0,
-                                       hdr[kHdrSymOk] != 0, group);
-    __syncthreads();
-    if (threadIdx.x < kClasses && blk[threadIdx.x])
-        atomicAdd(&hdr[kHdrBucketCount + threadIdx.x], blk[threadIdx.x]);
-}
-
-// Class bases, heaviest class first; resets cursors and queue counters.
-__global__ void k_items_base(uint32_t *hdr, uint32_t magic)
-{
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int cls = kClasses - 1; cls >= 0; --cls) {
-            hdr[kHdrBucketBase + cls] = run;
-            run += hdr[kHdrBucketCount + cls];
-        }
-        hdr[kHdrNItems] = hdr[kHdrMagic] == magic ? run : 0u;
-    }
-    if (threadIdx.x < kClasses) hdr[kHdrBucketCursor + threadIdx.x] = 0;
-    if (threadIdx.x < kQueues) hdr[kHdrQueue + 32 * threadIdx.x] = 0;
-}
-
-template <class Acc, bool kActiveOnly>
-__global__ __launch_bounds__(256) void k_items_write(Acc acc, int NC, const int *__restrict__ start,
-                                                     const int *__restrict__ nact,
-                                                     const uint32_t *__restrict__ info,
-                                                     uint32_t *hdr, int4 *__restrict__ items,
-                                                     int two, int group)
-{
-    __shared__ uint32_t cnt[kClasses];
-    __shared__ uint32_t base[kClasses];
-    if (threadIdx.x < kClasses) cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t inf = c < NC ? info[c] : 0u;
-    const int n_items = (int)(inf >> 5);
-    const int cls = (int)(inf & 31);
-    uint32_t local = 0;
-    if (inf) local = atomicAdd(&cnt[cls], (uint32_t)n_items);
-    __syncthreads();
-    if (threadIdx.x < kClasses && cnt[threadIdx.x])
-        base[threadIdx.x] = hdr[kHdrBucketBase + threadIdx.x] +
-                            atomicAdd(&hdr[kHdrBucketCursor + threadIdx.x], cnt[threadIdx.x]);
-    __syncthreads();
-    if (!inf) return;
-    const int na = nact[c];
-    const int nt = start[c + 1] - start[c];
-    const int seg = acc.seg_of_cell(c);
-    const uint32_t at = base[cls] + local;
-    const int s0 = start[c];
-    // active targets (all sources), then for the adjoint the passive ones (active sources);
-    // with symmetric tiles only the non-dense targets, against the non-dense sources
-    const int sym = hdr[kHdrSymOk] != 0 ? 1 : 0;
-    const int dn = sym ? dense_count(na) : 0;
-    const int k = write_run(items, at, c, s0 + dn, na - dn, two, seg, 0, sym, group);
-    if (!kActiveOnly) write_run(items, at + k, c, s0 + na, nt - na, two, seg, 1, sym, group);
 }
 
 // --------------------------------------------------------------- pair kernels
@@ -1458,199 +1319,393 @@ __device__ __forceinline__ void full_dir(int f, int &dx, int &dy, int &dz)
     dz = f % 3 - 1;
 }
 
-// Per cell c, the partial-slot counts of its row of kSymStride groups: [0]
-// target slots (items per run, each R consecutive windows, times its dense
-// particles); [1 + e] source slots
-// of its dense particles for direction e of the half stencil (runs of the
-// cell c - dir_e times the dense particles); [15 + f] source slots of its
-// non-dense particles for direction f of the full stencil (runs of the cell
-// c - dir_f times the non-dense particles).  Stored as the row's exclusive
-// prefix sums in pref and the row total in tot[c]; a scan of tot gives each
-// cell's first slot, so group e of cell c starts at base[c] + pref[c][e].
-// Also the item count and cost class of c as a home cell (runs times window
-// groups) in info[c], and the slot total of all cells (int64, header).  The
-// workgroup's rows are assembled in LDS and stored as one contiguous run.
+// Shape of the symmetric items.  An item of K blocks and R windows of W sources
+// is up to K R W tile steps of one wave, and every dense particle has one
+// target slot per R windows and every source one slot per run of K blocks: a
+// large shape needs few slots but leaves the chip to a few long items when
+// there is little work.  k_sym_plan adds up, for each shape of a list from the
+// configured one (K, R) to finer ones, the partial slots and the longest item;
+// its last workgroup takes the first shape whose work per wave of the
+// persistent grid is at least kSymSpread balance longest items, else the
+// finest one whose work still gives four waves per CU balance longest items
+// (an item that short costs less alone on its SIMD than the one-sided items,
+// of 64 targets against every source, would), in both cases among those whose
+// slots fit the pool; with none the tiles stay off.  A step (forward and
+// adjoint), one shape of 16 blocks and two windows under the old rule (work per
+// wave at least one longest item, else one-sided) against this one: 100,003
+// clustered particles 1.31 -> 0.70 ms, 2.1 million 2.98 -> 2.88, the 2.1 million
+// with halos of 55,000 particles a cell 40 -> 21 (its slots now fit the pool),
+// 16.8 million 19.6 -> 19.0.  kSymSpread 3 / 6 / 10: 20.9 / 20.4 / 20.4 ms there
+// and 2.80 / 2.86 / 2.92 on the 2.1 million.
+constexpr int kSymSpread = 5;
+
+struct SymShapes {
+    int n, W;
+    int K[kSymShapes], R[kSymShapes];
+};
+
+// Dense and other particles of the 27 cells around a cell (0 outside an open
+// domain), direction f = 9 (dx + 1) + 3 (dy + 1) + dz + 1 (its opposite is
+// 26 - f), and their active particles; all loads are in flight together.
 template <class Acc>
-__global__ __launch_bounds__(256) void k_sym_count(Acc acc, int NC, const int *__restrict__ start,
-                                                   const int *__restrict__ nact, int K, int W, int R,
-                                                   int *__restrict__ pref, int *__restrict__ tot_out,
-                                                   uint32_t *__restrict__ info, uint32_t *hdr,
-                                                   uint32_t magic)
+__device__ __forceinline__ void stencil_counts(const SegParams &S, int c, const int *__restrict__ start,
+                                               const int *__restrict__ nact, int (&nd)[kSymNdDirs],
+                                               int (&nn)[kSymNdDirs], int64_t &active)
 {
-    __shared__ uint32_t blk[kClasses];
-    __shared__ unsigned long long tot, work;
-    __shared__ uint32_t longest;
-    __shared__ int rows[256 * kSymStride];
-    if (threadIdx.x < kClasses) blk[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        tot = 0;
-        work = 0;
-        longest = 0;
+    int ix, iy, iz;
+    decode_cell(S, c, ix, iy, iz);
+    active = 0;
+#pragma unroll
+    for (int f = 0; f < kSymNdDirs; ++f) {
+        int dx, dy, dz, b;
+        float sx, sy, sz;
+        full_dir(f, dx, dy, dz);
+        nd[f] = 0;
+        nn[f] = 0;
+        if (cell_at(S, ix, iy, iz, dx, dy, dz, b, sx, sy, sz)) {
+            const int na = nact[b];
+            nd[f] = dense_count(na);
+            nn[f] = start[b + 1] - start[b] - nd[f];
+            active += na;
+        }
+    }
+}
+
+// Sources of the virtual list of a cell with dense particles: the dense ones
+// of itself and the upper half of its stencil, the others of all 27 cells.
+__device__ __forceinline__ int64_t sym_sources(const int (&nd)[kSymNdDirs], const int (&nn)[kSymNdDirs])
+{
+    int64_t sv = 0;
+#pragma unroll
+    for (int f = 0; f < kSymNdDirs; ++f) sv += nn[f] + (f >= kSymNdDirs / 2 ? nd[f] : 0);
+    return sv;
+}
+
+__device__ __forceinline__ uint64_t wave_sum(uint64_t v)
+{
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o);
+    return v;
+}
+
+__device__ __forceinline__ uint64_t load_agent(const uint32_t *p)
+{
+    return __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Only cells with dense particles look at their stencil.  `few`: the waves the
+// finest shape has to keep busy.  At most kListBlocks workgroups stride over
+// the cells: their totals are atomic adds to one line, some 8 ns each (one
+// workgroup per 256 cells took 375 us on 1.26 million cells).
+constexpr unsigned kListBlocks = 512;
+
+template <class Acc>
+__global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__restrict__ start,
+                                                  const int *__restrict__ nact, SymShapes sh, uint32_t *hdr,
+                                                  uint32_t magic, unsigned long long cap, int waves, int few,
+                                                  double balance)
+{
+    __shared__ unsigned long long slots[kSymShapes], work;
+    __shared__ uint32_t longest[kSymShapes], rank;
+    if (threadIdx.x < kSymShapes) {
+        slots[threadIdx.x] = 0;
+        longest[threadIdx.x] = 0;
+    }
+    if (threadIdx.x == 0) work = 0;
+    __syncthreads();
+    const bool binned = hdr[kHdrMagic] == magic;
+    for (int c0 = blockIdx.x * 256; binned && c0 < NC; c0 += gridDim.x * 256) {
+        const int c = c0 + threadIdx.x;
+        const int D = c < NC ? dense_count(nact[c]) : 0;
+        if (__ballot(D > 0) != 0ull) {
+            int64_t sv = 0;
+            if (D > 0) {
+                int nd[kSymNdDirs], nn[kSymNdDirs];
+                int64_t active;
+                stencil_counts<Acc>(acc.get(acc.seg_of_cell(c)), c, start, nact, nd, nn, active);
+                sv = sym_sources(nd, nn);
+            }
+            const int nb = D / kWave;
+            const bool first = (threadIdx.x & (kWave - 1)) == 0;
+            // tile steps: every block meets every source
+            const uint64_t steps = wave_sum((uint64_t)nb * (uint64_t)sv);
+            if (first) atomicAdd(&work, (unsigned long long)steps);
+            for (int i = 0; i < sh.n; ++i) {
+                const uint32_t rw = (uint32_t)(sh.R[i] * sh.W), k = (uint32_t)sh.K[i];
+                const uint64_t items = ((uint32_t)sv + rw - 1) / rw;  // per run; sv < 2^31
+                const uint64_t runs = ((uint32_t)nb + k - 1) / k;
+                uint64_t need = items * (uint64_t)D + runs * (uint64_t)sv;
+                if (items * runs >= (uint64_t(1) << 27)) need = uint64_t(1) << 42;  // beyond any pool
+                uint32_t cost = (uint32_t)min((uint64_t)min((uint32_t)nb, k) * min((uint64_t)rw, (uint64_t)sv),
+                                              (uint64_t)UINT32_MAX);
+                need = wave_sum(need);
+#pragma unroll
+                for (int o = kWave / 2; o >= 1; o >>= 1) cost = max(cost, (uint32_t)__shfl_xor((int)cost, o));
+                if (first) {
+                    atomicAdd(&slots[i], (unsigned long long)need);
+                    atomicMax(&longest[i], cost);
+                }
+            }
+        }
     }
     __syncthreads();
-    const bool ok = hdr[kHdrMagic] == magic;
-    const int c0 = blockIdx.x * 256;
-    const int c = c0 + threadIdx.x;
-    if (c < NC) {
-        int *row = rows + kSymStride * threadIdx.x;
-        uint32_t inf = 0;
-        unsigned long long slots = 0;
-        if (ok) {
-            const int D = dense_count(nact[c]);
-            const int ND = start[c + 1] - start[c] - D;
-            const SegParams &S = acc.get(acc.seg_of_cell(c));
-            int ix, iy, iz;
-            decode_cell(S, c, ix, iy, iz);
-            // dense and non-dense counts of the 27 cells of the stencil (0
-            // outside an open domain), all loads in flight together; every
-            // group below reads them from here
-            int nd[kSymNdDirs], nn[kSymNdDirs];
-#pragma unroll
-            for (int f = 0; f < kSymNdDirs; ++f) {
-                int dx, dy, dz, b;
-                float sx, sy, sz;
-                full_dir(f, dx, dy, dz);
-                nd[f] = 0;
-                nn[f] = 0;
-                if ((D > 0 || ND > 0) && cell_at(S, ix, iy, iz, dx, dy, dz, b, sx, sy, sz)) {
-                    nd[f] = dense_count(nact[b]);
-                    nn[f] = start[b + 1] - start[b] - nd[f];
-                }
-            }
-            // direction (dx, dy, dz) is full-stencil index f = 9 (dx + 1) + 3 (dy + 1) + dz + 1,
-            // and its opposite 26 - f
-            auto runs_of = [&](int f) { return (nd[f] / kWave + K - 1) / K; };
-            int64_t sv = 0;
-#pragma unroll
-            for (int e = 0; e < kSymDirs; ++e) {
-                int dx, dy, dz;
-                half_dir(e, dx, dy, dz);
-                const int f = 9 * (dx + 1) + 3 * (dy + 1) + dz + 1;
-                int64_t sc = 0;
-                if (D > 0) {
-                    sv += nd[f];
-                    sc = (int64_t)runs_of(kSymNdDirs - 1 - f) * D;
-                }
-                row[1 + e] = (int)min(sc, (int64_t)INT32_MAX);
-                slots += (unsigned long long)sc;
-            }
-#pragma unroll
-            for (int f = 0; f < kSymNdDirs; ++f) {
-                if (D > 0) sv += nn[f];
-                int64_t sc = 0;
-                if (ND > 0) sc = (int64_t)runs_of(kSymNdDirs - 1 - f) * ND;
-                row[1 + kSymDirs + f] = (int)min(sc, (int64_t)INT32_MAX);
-                slots += (unsigned long long)sc;
-            }
-            row[0] = 0;
-            if (D > 0) {
-                const int nb = D / kWave;
-                const int64_t C = (sv + W - 1) / W;         // windows
-                const int64_t CR = (C + R - 1) / R;         // items per run: R windows each
-                const int64_t G = (nb + K - 1) / K;
-                row[0] = (int)min(CR * D, (int64_t)INT32_MAX);
-                slots += (unsigned long long)(CR * D);
-                const int64_t n_items = G * CR;
-                // tile steps of the widest item: its blocks times its windows
-                int64_t cost = (int64_t)min(nb, K) * min((int64_t)R * W, sv);
-                if (cost < 1) cost = 1;
-                int cls = 63 - __clzll((unsigned long long)cost);
-                cls = cls > 31 ? 31 : cls;
-                if (n_items < (int64_t(1) << 27)) {
-                    inf = ((uint32_t)n_items << 5) | (uint32_t)cls;
-                    atomicAdd(&blk[cls], (uint32_t)n_items);
-                    // every block of the cell meets every source of its list once
-                    atomicAdd(&work, (unsigned long long)nb * (unsigned long long)sv);
-                    atomicMax(&longest, (uint32_t)min(cost, (int64_t)UINT32_MAX));
-                } else {
-                    slots = ~0ull >> 2;  // beyond any pool: the symmetric tiles stay off
-                }
-            }
-        } else {
+    if (threadIdx.x < sh.n && slots[threadIdx.x]) {
+        atomicAdd((unsigned long long *)&hdr[kHdrSymSlots + 2 * threadIdx.x], slots[threadIdx.x]);
+        atomicMax(&hdr[kHdrSymLongest + threadIdx.x], longest[threadIdx.x]);
+    }
+    if (threadIdx.x == 0 && work) atomicAdd((unsigned long long *)&hdr[kHdrSymWork], work);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) rank = atomicAdd(&hdr[kHdrSymDone], 1u);
+    __syncthreads();
+    if (rank != gridDim.x - 1 || threadIdx.x != 0) return;
+    __threadfence();
+    const double w = (double)load_agent(&hdr[kHdrSymWork]);
+    int pick = -1;
+    if (w > 0.0) {
+        auto fits = [&](int i) { return load_agent(&hdr[kHdrSymSlots + 2 * i]) <= cap; };
+        auto len = [&](int i) {
+            return (double)__hip_atomic_load(&hdr[kHdrSymLongest + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        for (int i = 0; i < sh.n && pick < 0; ++i)
+            if (fits(i) && w >= kSymSpread * balance * waves * len(i)) pick = i;
+        for (int i = sh.n - 1; i >= 0 && pick < 0; --i)
+            if (fits(i) && w >= balance * few * len(i)) pick = i;
+    }
+    if (pick >= 0) {
+        hdr[kHdrSymK] = (uint32_t)sh.K[pick];
+        hdr[kHdrSymR] = (uint32_t)sh.R[pick];
+        hdr[kHdrSymOk] = 1u;
+    }
+}
+
+// Per home cell: its one-sided items and their cost class (floor log2 of the
+// pairs one lane evaluates) in info[c], and, when the symmetric tiles run,
+// its symmetric items and class in sym_info[c] and its partial slots; items are
+// counted per class.
+//
+// One-sided: the forward takes the cell's active targets against every source
+// of the 27 cells.  The adjoint also takes its passive targets, as items of
+// their own whose sources are only the active particles of the 27 cells: a
+// pair of two passive particles has u = m_k g_j - m_j g_k = 0, so it adds
+// exactly nothing.  With symmetric tiles the dense blocks have no item here,
+// and the other targets take only the non-dense sources (the tiles give them
+// the terms of the dense ones).
+//
+// Slots: cell c has a row of kSymStride groups: [0] target slots (items per
+// run, each R consecutive windows, times its dense particles); [1 + e] source
+// slots of its dense particles for direction e of the half stencil (runs of
+// the cell c - dir_e times the dense particles); [15 + f] source slots of its
+// non-dense particles for direction f of the full stencil (runs of the cell
+// c - dir_f times the non-dense particles).  pref holds the row's exclusive
+// prefix sums and tot[c] its total; group e starts at slot base[c] +
+// pref[c][e].  A workgroup takes the slots of its cells from a counter: where
+// a cell's slots lie does not matter to any sum.  Only rows with slots are
+// written: nothing reads the others.  The cells of a workgroup are assembled
+// in LDS and stored as one contiguous run.
+constexpr int kCellThreads = 128;
+
+template <class Acc, bool kActiveOnly>
+__global__ __launch_bounds__(kCellThreads) void k_cells(
+    Acc acc, int NC, const int *__restrict__ start, const int *__restrict__ nact, uint32_t *__restrict__ info,
+    uint32_t *__restrict__ sym_info, int *__restrict__ pref, int *__restrict__ tot_out, int *__restrict__ base_out,
+    uint32_t *hdr, uint32_t magic, int N, int two, int group, int W)
+{
+    __shared__ uint32_t blk[kClasses], sblk[kClasses];
+    __shared__ int rows[kCellThreads * kSymStride];
+    __shared__ int wsum[kCellThreads / kWave], slot0;
+    const int tid = threadIdx.x;
+    if (tid < kClasses) {
+        blk[tid] = 0;
+        sblk[tid] = 0;
+    }
+    __syncthreads();
+    const bool binned = hdr[kHdrMagic] == magic;
+    const bool sym = hdr[kHdrSymOk] != 0;
+    const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
+    const int lane = tid & (kWave - 1), wv = tid / kWave;
+    if (!binned && blockIdx.x == 0 && tid == 0) atomicOr(&hdr[kHdrFlags], (uint32_t)SR_FLAG_NOT_BINNED);
+    int *row = rows + kSymStride * tid;
+    for (int c0 = blockIdx.x * kCellThreads; c0 < NC; c0 += gridDim.x * kCellThreads) {
+        const int c = c0 + tid;
+        uint32_t inf = 0, sinf = 0;
+        int total = 0;
+        if (sym) {
+#pragma unroll 1
             for (int e = 0; e < kSymStride; ++e) row[e] = 0;
         }
-        // counts to exclusive prefixes; a total past 2^31 - 1 exceeds every pool
-        // (the header's int64 total turns the tiles off), so clamping is harmless
-        int64_t run = 0;
-        for (int e = 0; e < kSymStride; ++e) {
-            const int v = row[e];
-            row[e] = (int)min(run, (int64_t)INT32_MAX);
-            run += v;
+        const int na = binned && c < NC ? nact[c] : 0;
+        const int nc = binned && c < NC ? start[c + 1] - start[c] : 0;
+        if (nc > 0 && na >= 0 && na <= nc && nc <= N) {
+            const int np = kActiveOnly ? 0 : nc - na;
+            int nd[kSymNdDirs], nn[kSymNdDirs];
+            int64_t src_act;
+            stencil_counts<Acc>(acc.get(acc.seg_of_cell(c)), c, start, nact, nd, nn, src_act);
+            int64_t src = 0, src_nd = 0, src_d = 0;
+#pragma unroll
+            for (int f = 0; f < kSymNdDirs; ++f) {
+                src_d += nd[f];
+                src_nd += nn[f];
+            }
+            src = src_nd + src_d;
+            const int64_t sv = sym_sources(nd, nn);
+            const int D = sym ? dense_count(na) : 0;
+            // cost class from the cell's widest item: a group of min(targets, group) when sparse
+            const int n_items = cell_items(na - D, two != 0, group) + cell_items(np, two != 0, group);
+            int64_t cost = max(run_cost(na - D, sym ? src_nd : src, two != 0, group),
+                               run_cost(np, sym ? src_act - src_d : src_act, two != 0, group));
+            cost = cost < 1 ? 1 : cost;
+            const int cls = min(63 - __clzll((unsigned long long)cost), 31);
+            inf = ((uint32_t)n_items << 5) | (uint32_t)cls;
+            // per-block class totals, one global atomic per class and block
+            if (n_items) atomicAdd(&blk[cls], (uint32_t)n_items);
+            if (sym) {
+                const int ND = nc - D;
+                // runs of each cell of the stencil (blocks / K rounded up, as a product: exact for K <= 256
+                // and fewer than 2^26 blocks)
+                const uint64_t inv_k = ((uint64_t(1) << 36) + K - 1) / (uint64_t)K;
+#pragma unroll
+                for (int f = 0; f < kSymNdDirs; ++f)
+                    nd[f] = (int)(((uint64_t)(uint32_t)(nd[f] / kWave + K - 1) * inv_k) >> 36);
+                // counts, then exclusive prefixes; k_sym_plan has checked that all of them fit the pool
+                if (D > 0) {
+                    const int nb = D / kWave;
+                    const int per_run = (int)(((uint32_t)sv + (uint32_t)(R * W) - 1u) / (uint32_t)(R * W));
+                    const int n_sym = nd[kSymNdDirs / 2] * per_run;
+                    int64_t scost = (int64_t)min(nb, K) * min((int64_t)R * W, sv);
+                    scost = scost < 1 ? 1 : scost;
+                    const int scls = min(63 - __clzll((unsigned long long)scost), 31);
+                    sinf = ((uint32_t)n_sym << 5) | (uint32_t)scls;
+                    if (n_sym) atomicAdd(&sblk[scls], (uint32_t)n_sym);
+                    row[0] = per_run * D;
+                }
+#pragma unroll
+                for (int e = 0; e < kSymDirs; ++e) {
+                    int dx, dy, dz;
+                    half_dir(e, dx, dy, dz);
+                    const int f = 9 * (dx + 1) + 3 * (dy + 1) + dz + 1;
+                    row[1 + e] = nd[kSymNdDirs - 1 - f] * D;
+                }
+#pragma unroll
+                for (int f = 0; f < kSymNdDirs; ++f) {
+                    row[1 + kSymDirs + f] = nd[kSymNdDirs - 1 - f] * ND;
+                }
+#pragma unroll 1
+                for (int e = 0; e < kSymStride; ++e) {
+                    const int v = row[e];
+                    row[e] = total;
+                    total += v;
+                }
+            }
         }
-        tot_out[c] = (int)min(run, (int64_t)INT32_MAX);
-        info[c] = inf;
-        if (slots) atomicAdd(&tot, slots);
+        if (c < NC) info[c] = inf;
+        if (!sym) continue;
+        // this workgroup's slots
+        int incl = total;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int y = __shfl_up(incl, d);
+            if (lane >= d) incl += y;
+        }
+        if (lane == kWave - 1) wsum[wv] = incl;
+        __syncthreads();
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kCellThreads / kWave; ++w) {
+            before += w < wv ? wsum[w] : 0;
+            all += wsum[w];
+        }
+        if (tid == 0) slot0 = all ? (int)atomicAdd(&hdr[kHdrSymAlloc], (uint32_t)all) : 0;
+        __syncthreads();
+        if (c < NC) {
+            sym_info[c] = sinf;
+            tot_out[c] = total;
+            base_out[c] = slot0 + before + incl - total;
+        }
+        if (all != 0) {
+            const int n = min(kCellThreads, NC - c0) * kSymStride;
+            int *out = pref + (int64_t)kSymStride * c0;
+            for (int i = tid; i < n; i += kCellThreads) out[i] = rows[i];
+        }
+        __syncthreads();  // before the next cells' rows
     }
     __syncthreads();
-    const int nrow = min(256, NC - c0);
-    int *out = pref + (int64_t)kSymStride * c0;
-    for (int i = threadIdx.x; i < nrow * kSymStride; i += 256) out[i] = rows[i];
-    if (threadIdx.x < kClasses && blk[threadIdx.x])
-        atomicAdd(&hdr[kHdrSymBucketCount + threadIdx.x], blk[threadIdx.x]);
-    if (threadIdx.x == 0) {
-        if (tot) atomicAdd((unsigned long long *)&hdr[kHdrSymTotal], tot);
-        if (work) atomicAdd((unsigned long long *)&hdr[kHdrSymWork], work);
-        if (longest) atomicMax(&hdr[kHdrSymMaxItem], longest);
-    }
+    if (tid < kClasses && blk[tid]) atomicAdd(&hdr[kHdrBucketCount + tid], blk[tid]);
+    if (tid < kClasses && sblk[tid]) atomicAdd(&hdr[kHdrSymBucketCount + tid], sblk[tid]);
 }
 
-// Class bases of the symmetric items, heaviest first; the tiles run only when
-// enabled, on bins of these sizes, when every partial slot fits the pool, and
-// when their work spread over the persistent grid (waves) is at least
-// balance times the longest item: otherwise a few long items would leave most
-// waves idle, and the one-sided kernels, with items of at most 64 targets,
-// finish sooner.
-__global__ void k_sym_base(uint32_t *hdr, uint32_t magic, long long cap, int enabled, int waves,
-                           double balance)
+// First item of each cost class (heaviest class first) from the class counts,
+// computed by every workgroup; this workgroup's cells of class cls start at
+// base[cls].  Returns the number of items.
+__device__ __forceinline__ uint32_t class_bases(const uint32_t *counts, uint32_t *cursors, const uint32_t *mine,
+                                                uint32_t *base)
 {
-    if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    if (threadIdx.x < kClasses) {
+        const int cls = threadIdx.x;
         uint32_t run = 0;
-        for (int cls = kClasses - 1; cls >= 0; --cls) {
-            hdr[kHdrSymBucketBase + cls] = run;
-            run += hdr[kHdrSymBucketCount + cls];
+        for (int k = kClasses - 1; k >= 0; --k) {
+            const uint32_t n = counts[k];
+            if (k > cls) run += n;
+            total += n;
         }
-        const unsigned long long tot = *(const unsigned long long *)&hdr[kHdrSymTotal];
-        const double work = (double)*(const unsigned long long *)&hdr[kHdrSymWork];
-        const bool spread = work >= balance * (double)waves * (double)hdr[kHdrSymMaxItem];
-        const bool ok = enabled && hdr[kHdrMagic] == magic && run > 0 && tot <= (unsigned long long)cap &&
-                        spread;
-        hdr[kHdrSymOk] = ok ? 1u : 0u;
-        hdr[kHdrSymNItems] = ok ? run : 0u;
+        base[cls] = run + (mine[cls] ? atomicAdd(&cursors[cls], mine[cls]) : 0u);
     }
-    if (threadIdx.x < kClasses) hdr[kHdrSymBucketCursor + threadIdx.x] = 0;
-    if (threadIdx.x < kQueues) hdr[kHdrSymQueue + 32 * threadIdx.x] = 0;
+    return total;
 }
 
-// Symmetric items (A, run, window, problem), in cost-class order.
-template <class Acc>
-__global__ __launch_bounds__(256) void k_sym_write(Acc acc, int NC, const int *__restrict__ nact,
-                                                   int K, const uint32_t *__restrict__ info,
-                                                   uint32_t *hdr, int4 *__restrict__ items)
+// The items of every cell, in cost-class order: one-sided ones, and symmetric
+// ones (cell, run, window group, problem).
+template <class Acc, bool kActiveOnly>
+__global__ __launch_bounds__(256) void k_items_write(Acc acc, int NC, const int *__restrict__ start,
+                                                     const int *__restrict__ nact,
+                                                     const uint32_t *__restrict__ info,
+                                                     const uint32_t *__restrict__ sym_info, uint32_t *hdr,
+                                                     int4 *__restrict__ items, int4 *__restrict__ sym_items,
+                                                     int two, int group)
 {
-    __shared__ uint32_t cnt[kClasses];
-    __shared__ uint32_t base[kClasses];
-    if (hdr[kHdrSymOk] == 0) return;  // uniform over the block
-    if (threadIdx.x < kClasses) cnt[threadIdx.x] = 0;
+    __shared__ uint32_t cnt[2][kClasses];
+    __shared__ uint32_t base[2][kClasses];
+    if (threadIdx.x < 2 * kClasses) cnt[threadIdx.x / kClasses][threadIdx.x % kClasses] = 0;
+    const bool sym = hdr[kHdrSymOk] != 0;
     __syncthreads();
     const int c = blockIdx.x * 256 + threadIdx.x;
     const uint32_t inf = c < NC ? info[c] : 0u;
-    const int n_items = (int)(inf >> 5);
-    const int cls = (int)(inf & 31);
-    uint32_t local = 0;
-    if (inf) local = atomicAdd(&cnt[cls], (uint32_t)n_items);
+    const uint32_t sinf = sym && c < NC ? sym_info[c] : 0u;
+    const int n_items = (int)(inf >> 5), n_sym = (int)(sinf >> 5);
+    const int cls = (int)(inf & 31), scls = (int)(sinf & 31);
+    uint32_t local = 0, slocal = 0;
+    if (n_items) local = atomicAdd(&cnt[0][cls], (uint32_t)n_items);
+    if (n_sym) slocal = atomicAdd(&cnt[1][scls], (uint32_t)n_sym);
     __syncthreads();
-    if (threadIdx.x < kClasses && cnt[threadIdx.x])
-        base[threadIdx.x] = hdr[kHdrSymBucketBase + threadIdx.x] +
-                            atomicAdd(&hdr[kHdrSymBucketCursor + threadIdx.x], cnt[threadIdx.x]);
+    const uint32_t all = class_bases(hdr + kHdrBucketCount, hdr + kHdrBucketCursor, cnt[0], base[0]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) hdr[kHdrNItems] = all;
+    if (sym) {
+        const uint32_t sall = class_bases(hdr + kHdrSymBucketCount, hdr + kHdrSymBucketCursor, cnt[1], base[1]);
+        if (blockIdx.x == 0 && threadIdx.x == 0) hdr[kHdrSymNItems] = sall;
+    }
     __syncthreads();
-    if (!inf) return;
-    const int nb = dense_count(nact[c]) / kWave;
-    const int G = (nb + K - 1) / K;
-    const int C = n_items / G;
+    if (n_items == 0 && n_sym == 0) return;
+    const int na = nact[c];
     const int seg = acc.seg_of_cell(c);
-    const uint32_t at = base[cls] + local;
-    for (int g = 0; g < G; ++g)
-        for (int k = 0; k < C; ++k) items[at + (uint32_t)(g * C + k)] = make_int4(c, g, k, seg);
+    const int dn = sym ? dense_count(na) : 0;
+    if (n_items) {
+        const int nt = start[c + 1] - start[c];
+        const uint32_t at = base[0][cls] + local;
+        const int s0 = start[c];
+        // active targets (all sources), then for the adjoint the passive ones (active sources);
+        // with symmetric tiles only the non-dense targets, against the non-dense sources
+        const int k = write_run(items, at, c, s0 + dn, na - dn, two, seg, 0, sym ? 1 : 0, group);
+        if (!kActiveOnly) write_run(items, at + k, c, s0 + na, nt - na, two, seg, 1, sym ? 1 : 0, group);
+    }
+    if (n_sym) {
+        const int K = (int)hdr[kHdrSymK];
+        const int G = (dn / kWave + K - 1) / K;
+        const int C = n_sym / G;
+        const uint32_t at = base[1][scls] + slocal;
+        for (int g = 0; g < G; ++g)
+            for (int k = 0; k < C; ++k) sym_items[at + (uint32_t)(g * C + k)] = make_int4(c, g, k, seg);
+    }
 }
 
 // The source segments of a symmetric item, one per lane: lanes 0..13 the
@@ -1966,7 +2021,7 @@ __device__ __forceinline__ void force_sym_items(const Acc &acc, const int4 *__re
                                                 const int *__restrict__ nact,
                                                 const int *__restrict__ sym_base,
                                                 const int *__restrict__ sym_pref, const Src &src,
-                                                float *__restrict__ pool, int K, int R, float4 *tile,
+                                                float *__restrict__ pool, float4 *tile,
                                                 int *tix, SymRed<kW> &red, int64_t pull_limit)
 {
     const int lane = threadIdx.x;
@@ -1974,6 +2029,7 @@ __device__ __forceinline__ void force_sym_items(const Acc &acc, const int4 *__re
     // tiles off (or nothing to do): leave before touching the queues, which
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
+    const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
     const int q0 = blockIdx.x & (kQueues - 1);
     PullGuard guard(min(n_items, pull_limit));
     for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
@@ -2131,16 +2187,16 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_force_sym(Acc acc, 
                                                   const int *__restrict__ nact,
                                                   const int *__restrict__ sym_base,
                                                   const int *__restrict__ sym_pref, Src src,
-                                                  float *__restrict__ pool, int K, int R, int64_t pull_limit)
+                                                  float *__restrict__ pool, int64_t pull_limit)
 {
     __shared__ float4 tile[2 * kWave];
     __shared__ int tix[kWave];
     __shared__ SymRed<kW> red;
     if (hdr[kHdrMassInfo] == 0)
-        force_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool, K, R,
+        force_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool,
                                               tile, tix, red, pull_limit);
     else
-        force_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool, K, R,
+        force_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool,
                                                tile, tix, red, pull_limit);
 }
 
@@ -2154,7 +2210,7 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
                                               const int *__restrict__ sym_pref, const Src &src,
                                               const float *__restrict__ gx, const float *__restrict__ gy,
                                               const float *__restrict__ gz, float *__restrict__ pool,
-                                              int K, int R, float4 *tile_p, float4 *tile_g, int *tix,
+                                              float4 *tile_p, float4 *tile_g, int *tix,
                                               SymRed<kW> &red, int64_t pull_limit)
 {
     const int lane = threadIdx.x;
@@ -2162,6 +2218,7 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
     // tiles off (or nothing to do): leave before touching the queues, which
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
+    const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
     const int q0 = blockIdx.x & (kQueues - 1);
     PullGuard guard(min(n_items, pull_limit));
     for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
@@ -2321,19 +2378,19 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_vjp_sym(Acc acc, co
                                                 const int *__restrict__ sym_base,
                                                 const int *__restrict__ sym_pref, Src src,
                                                 const float *__restrict__ gx, const float *__restrict__ gy,
-                                                const float *__restrict__ gz, float *__restrict__ pool, int K,
-                                                int R, int64_t pull_limit)
+                                                const float *__restrict__ gz, float *__restrict__ pool,
+                                                int64_t pull_limit)
 {
     __shared__ float4 tile_p[2 * kWave];
     __shared__ float4 tile_g[2 * kWave];
     __shared__ int tix[kWave];
     __shared__ SymRed<kW> red;
     if (hdr[kHdrMassInfo] == 0)
-        vjp_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool, K,
-                                            R, tile_p, tile_g, tix, red, pull_limit);
+        vjp_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool,
+                                            tile_p, tile_g, tix, red, pull_limit);
     else
-        vjp_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool, K,
-                                             R, tile_p, tile_g, tix, red, pull_limit);
+        vjp_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool,
+                                             tile_p, tile_g, tix, red, pull_limit);
 }
 
 // Adds up the partial slots of every particle, in a fixed order.  A dense
@@ -2350,6 +2407,7 @@ __global__ __launch_bounds__(256) void k_sym_gather(int N, int key_bits, const i
                                                     const int *__restrict__ nact,
                                                     const int *__restrict__ sym_pref,
                                                     const int *__restrict__ sym_base,
+                                                    const int *__restrict__ sym_tot,
                                                     const float *__restrict__ pool,
                                                     const int *__restrict__ rows,
                                                     const float *__restrict__ mass /*binned*/,
@@ -2361,6 +2419,8 @@ __global__ __launch_bounds__(256) void k_sym_gather(int N, int key_bits, const i
     const int r = rows[b];
     if (r < 0 || r >= n_out) return;
     const int c = key[b] >> key_bits;
+    const int ctot = sym_tot[c];
+    if (ctot == 0) return;  // no tile reaches this cell
     const int jl = b - start[c];
     const int D = dense_count(nact[c]);
     const bool dense = jl < D;
@@ -2368,7 +2428,7 @@ __global__ __launch_bounds__(256) void k_sym_gather(int N, int key_bits, const i
     const int j = dense ? jl : jl - D;
     const int e0 = dense ? 0 : 1 + kSymDirs, e1 = dense ? 1 + kSymDirs : kSymStride;
     const int *pf = sym_pref + (int64_t)kSymStride * c;
-    const int cb = sym_base[c], ctot = sym_base[c + 1] - cb;
+    const int cb = sym_base[c];
     struct F3 {
         float x, y, z;
     };
@@ -2499,66 +2559,77 @@ bool all_softened(const DevArgs &a)
     return a.seg_host->pc.softened != 0;
 }
 
-template <bool kActiveOnly>
-hipError_t build_items(const DevArgs &a, int two)
-{
-    const Layout &L = *a.L;
-    uint32_t *hdr = at<uint32_t>(a, L.hdr);
-    hipError_t e = fill_u32(hdr + kHdrBucketCount, kClasses, 0, a.st);
-    if (e != hipSuccess) return e;
-    return with_acc(a, [&](auto acc) -> hipError_t {
-        const unsigned nb = blocks_for(L.NC, 256);
-        k_items_count<decltype(acc), kActiveOnly><<<nb, 256, 0, a.st>>>(
-            acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), at<uint32_t>(a, L.info), hdr,
-            L.magic(), (int)L.N, two, a.sparse_group);
-        k_items_base<<<1, 64, 0, a.st>>>(hdr, L.magic());
-        k_items_write<decltype(acc), kActiveOnly><<<nb, 256, 0, a.st>>>(
-            acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), at<uint32_t>(a, L.info), hdr,
-            at<int4>(a, L.items), two, a.sparse_group);
-        return hipGetLastError();
-    });
-}
-
-// Symmetric tiles: partial-slot counts and the scan of their cell totals, the go/no-go decision
-// (hdr[kHdrSymOk]) and the items.  Must precede build_items, whose dense
-// items then take only the non-dense sources.  With the tiles switched off
-// the decision is no.
-unsigned persistent_grid(const DevArgs &a);
-
-hipError_t build_sym(const DevArgs &a)
-{
-    const Layout &L = *a.L;
-    uint32_t *hdr = at<uint32_t>(a, L.hdr);
-    hipError_t e = fill_u32(hdr + kHdrSymTotal, 7, 0, a.st);  // total, ok, n_items, work, longest
-    if (e != hipSuccess || a.sym_blocks <= 0) return e;
-    if ((e = fill_u32(hdr + kHdrSymBucketCount, kClasses, 0, a.st)) != hipSuccess) return e;
-    const int W = a.sym_window;
-    return with_acc(a, [&](auto acc) -> hipError_t {
-        const unsigned nb = blocks_for(L.NC, 256);
-        k_sym_count<<<nb, 256, 0, a.st>>>(acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact),
-                                          a.sym_blocks, W, a.sym_rounds,
-                                          at<int>(a, L.sym_pref), at<int>(a, L.sym_tot),
-                                          at<uint32_t>(a, L.sym_info), hdr, L.magic());
-        hipError_t e2 = hipGetLastError();
-        if (e2 != hipSuccess) return e2;
-        if ((e2 = scan_i32(at<int>(a, L.sym_tot), at<int>(a, L.sym_base), L.NC, at<int>(a, L.scan_tmp),
-                           a.st)) != hipSuccess)
-            return e2;
-        int64_t waves = persistent_grid(a);
-        if (waves > L.sym_item_cap) waves = L.sym_item_cap;
-        k_sym_base<<<1, 64, 0, a.st>>>(hdr, L.magic(), (long long)L.sym_cap, 1, (int)waves, a.sym_balance);
-        k_sym_write<<<nb, 256, 0, a.st>>>(acc, (int)L.NC, at<int>(a, L.nact), a.sym_blocks,
-                                          at<uint32_t>(a, L.sym_info), hdr, at<int4>(a, L.sym_items));
-        return hipGetLastError();
-    });
-}
-
 unsigned persistent_grid(const DevArgs &a)
 {
     int64_t g = (int64_t)a.num_cu * a.waves_per_cu;
     if (g > a.L->item_cap) g = a.L->item_cap;
     if (g < 1) g = 1;
     return (unsigned)g;
+}
+
+// Waves of the symmetric kernels, and those the finest shape has to keep busy.
+int sym_waves(const DevArgs &a)
+{
+    return (int)std::min<int64_t>(persistent_grid(a), a.L->sym_item_cap);
+}
+
+int sym_few(const DevArgs &a) { return std::min(sym_waves(a), 4 * a.num_cu); }
+
+// Whether the symmetric tiles can run at all: work over longest item is at
+// most the sum over cells of blocks times max(1, sources / W) (k_sym_plan), so
+// at most n / 64 max(1, n / W), and k_sym_plan asks for balance times few.
+bool sym_possible(const DevArgs &a)
+{
+    const double n = (double)a.L->N;
+    return a.sym_blocks > 0 && n / kWave * std::max(1.0, n / a.sym_window) >= a.sym_balance * sym_few(a);
+}
+
+// Work lists of a pass: with `sym`, the symmetric tiles' shape (or the
+// decision to leave them off), then every cell's items and partial slots.
+template <bool kActiveOnly>
+hipError_t build_lists(const DevArgs &a, int two, bool sym)
+{
+    const Layout &L = *a.L;
+    uint32_t *hdr = at<uint32_t>(a, L.hdr);
+    // counters, decisions and queues (everything after the flags, tag and mass words)
+    hipError_t e = fill_u32(hdr + kHdrBucketCount, kHdrWords - kHdrBucketCount, 0, a.st);
+    if (e != hipSuccess) return e;
+    return with_acc(a, [&](auto acc) -> hipError_t {
+        using A = decltype(acc);
+        if (sym) {
+            SymShapes sh{};
+            sh.W = a.sym_window;
+            auto add = [&](int k, int r) {
+                k = k < 1 ? 1 : k;
+                if (sh.n > 0 && sh.K[sh.n - 1] == k && sh.R[sh.n - 1] == r) return;
+                sh.K[sh.n] = k;
+                sh.R[sh.n++] = r;
+            };
+            add(a.sym_blocks, a.sym_rounds);
+            if (a.sym_balance > 0.0) {
+                add(a.sym_blocks / 2, a.sym_rounds);
+                add(a.sym_blocks / 4, a.sym_rounds);
+                add(a.sym_blocks / 4, 1);
+                add(a.sym_blocks / 8, 1);
+                add(a.sym_blocks / 16, 1);
+            }
+            k_sym_plan<<<std::min(blocks_for(L.NC, 256), kListBlocks), 256, 0, a.st>>>(
+                acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), sh, hdr, L.magic(),
+                (unsigned long long)L.sym_cap, sym_waves(a), sym_few(a), a.sym_balance);
+            const hipError_t e2 = hipGetLastError();
+            if (e2 != hipSuccess) return e2;
+        }
+        k_cells<A, kActiveOnly><<<std::min(blocks_for(L.NC, kCellThreads), 4 * kListBlocks), kCellThreads, 0, a.st>>>(
+            acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), at<uint32_t>(a, L.info),
+            at<uint32_t>(a, L.sym_info), at<int>(a, L.sym_pref), at<int>(a, L.sym_tot), at<int>(a, L.sym_base), hdr,
+            L.magic(), (int)L.N, two, a.sparse_group, a.sym_window);
+        hipError_t e2 = hipGetLastError();
+        if (e2 != hipSuccess) return e2;
+        k_items_write<A, kActiveOnly><<<blocks_for(L.NC, 256), 256, 0, a.st>>>(
+            acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), at<uint32_t>(a, L.info),
+            at<uint32_t>(a, L.sym_info), hdr, at<int4>(a, L.items), at<int4>(a, L.sym_items), two, a.sparse_group);
+        return hipGetLastError();
+    });
 }
 
 Src src_of(const DevArgs &a)
@@ -2682,15 +2753,13 @@ void launch_force_sym_v(const DevArgs &a, Acc acc, unsigned grid)
     const Layout &L = *a.L;
     k_force_sym<Acc, kSoft, kW, kOcc><<<grid, kWave, 0, a.st>>>(
         acc, at<int4>(a, L.sym_items), at<uint32_t>(a, L.hdr), at<int>(a, L.start), at<int>(a, L.nact),
-        at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<float>(a, L.sym_pool), a.sym_blocks,
-        a.sym_rounds, a.pull_limit);
+        at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<float>(a, L.sym_pool), a.pull_limit);
 }
 
 template <class Acc, bool kSoft>
 void launch_force_sym(const DevArgs &a, Acc acc)
 {
-    unsigned grid = persistent_grid(a);
-    if ((int64_t)grid > a.L->sym_item_cap) grid = (unsigned)a.L->sym_item_cap;
+    const unsigned grid = (unsigned)sym_waves(a);
     if (a.sym_window >= 512) {
         if (a.sym_occupancy >= 6) launch_force_sym_v<Acc, kSoft, 512, 6>(a, acc, grid);
         else if (a.sym_occupancy >= 5) launch_force_sym_v<Acc, kSoft, 512, 5>(a, acc, grid);
@@ -2709,14 +2778,13 @@ void launch_vjp_sym_v(const DevArgs &a, Acc acc, unsigned grid)
     k_vjp_sym<Acc, kSoft, kW, kOcc><<<grid, kWave, 0, a.st>>>(
         acc, at<int4>(a, L.sym_items), at<uint32_t>(a, L.hdr), at<int>(a, L.start), at<int>(a, L.nact),
         at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<float>(a, L.gx), at<float>(a, L.gy),
-        at<float>(a, L.gz), at<float>(a, L.sym_pool), a.sym_blocks, a.sym_rounds, a.pull_limit);
+        at<float>(a, L.gz), at<float>(a, L.sym_pool), a.pull_limit);
 }
 
 template <class Acc, bool kSoft>
 void launch_vjp_sym(const DevArgs &a, Acc acc)
 {
-    unsigned grid = persistent_grid(a);
-    if ((int64_t)grid > a.L->sym_item_cap) grid = (unsigned)a.L->sym_item_cap;
+    const unsigned grid = (unsigned)sym_waves(a);
     if (a.sym_window >= 512) {
         if (a.sym_occupancy >= 5) launch_vjp_sym_v<Acc, kSoft, 512, 5>(a, acc, grid);
         else launch_vjp_sym_v<Acc, kSoft, 512, 0>(a, acc, grid);
@@ -2732,16 +2800,16 @@ hipError_t sym_gather(const DevArgs &a, const int *rows, float *out, int n_out, 
     const Layout &L = *a.L;
     k_sym_gather<<<blocks_for(L.N, 256), 256, 0, a.st>>>(
         (int)L.N, L.key_bits, at<int>(a, L.sorted_keys()), at<int>(a, L.start), at<int>(a, L.nact),
-        at<int>(a, L.sym_pref), at<int>(a, L.sym_base), at<float>(a, L.sym_pool), rows, at<float>(a, L.bm),
+        at<int>(a, L.sym_pref), at<int>(a, L.sym_base), at<int>(a, L.sym_tot), at<float>(a, L.sym_pool), rows,
+        at<float>(a, L.bm),
         at<uint32_t>(a, L.hdr), out, n_out, scale);
     return hipGetLastError();
 }
 
 hipError_t dev_force(const DevArgs &a, float *acc_out)
 {
-    hipError_t e = build_sym(a);
-    if (e != hipSuccess) return e;
-    e = build_items<true>(a, a.targets_per_lane >= 2 ? 1 : 0);
+    const bool sym = sym_possible(a);
+    const hipError_t e = build_lists<true>(a, a.targets_per_lane >= 2 ? 1 : 0, sym);
     if (e != hipSuccess) return e;
     const bool soft = all_softened(a);
     return with_acc(a, [&](auto acc) -> hipError_t {
@@ -2758,7 +2826,7 @@ hipError_t dev_force(const DevArgs &a, float *acc_out)
             else launch_force<A, false, 0>(a, acc, acc_out);
         }
         hipError_t le = hipGetLastError();
-        if (le == hipSuccess && a.sym_blocks > 0) {
+        if (le == hipSuccess && sym) {
             // dense pairs once each; the device skips both when the tiles are off
             if (soft) launch_force_sym<A, true>(a, acc);
             else launch_force_sym<A, false>(a, acc);
@@ -2778,8 +2846,8 @@ hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad)
                                                       at<float>(a, L.gz));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if ((e = build_sym(a)) != hipSuccess) return e;
-    if ((e = build_items<false>(a, a.targets_per_lane >= 2 ? 1 : 0)) != hipSuccess) return e;
+    const bool sym = sym_possible(a);
+    if ((e = build_lists<false>(a, a.targets_per_lane >= 2 ? 1 : 0, sym)) != hipSuccess) return e;
     const bool soft = all_softened(a);
     return with_acc(a, [&](auto acc) -> hipError_t {
         using A = decltype(acc);
@@ -2794,7 +2862,7 @@ hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad)
             else launch_vjp<A, false, 0>(a, acc, grad);
         }
         hipError_t le = hipGetLastError();
-        if (le == hipSuccess && a.sym_blocks > 0) {
+        if (le == hipSuccess && sym) {
             if (soft) launch_vjp_sym<A, true>(a, acc);
             else launch_vjp_sym<A, false>(a, acc);
             if ((le = hipGetLastError()) == hipSuccess)
@@ -2813,14 +2881,10 @@ __global__ void k_copy_pairs(const uint32_t *hdr, int64_t *out)
 hipError_t dev_count_pairs(const DevArgs &a, bool adjoint, int64_t *pairs)
 {
     const Layout &L = *a.L;
-    // every ordered pair from its target's end: no symmetric tiles here
-    DevArgs one = a;
-    one.sym_blocks = 0;
-    hipError_t e = build_sym(one);
+    // every ordered pair from its target's end: no symmetric tiles here (the
+    // pair counter is zeroed with the lists)
+    hipError_t e = adjoint ? build_lists<false>(a, 0, false) : build_lists<true>(a, 0, false);
     if (e != hipSuccess) return e;
-    e = adjoint ? build_items<false>(a, 0) : build_items<true>(a, 0);
-    if (e != hipSuccess) return e;
-    if ((e = fill_u32(at<uint32_t>(a, L.hdr) + kHdrPairs, 2, 0, a.st)) != hipSuccess) return e;
     e = with_acc(a, [&](auto acc) -> hipError_t {
         k_count<<<persistent_grid(a), kWave, 0, a.st>>>(acc, at<int4>(a, L.items),
                                                        at<uint32_t>(a, L.hdr), at<int>(a, L.start),

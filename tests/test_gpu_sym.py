@@ -187,3 +187,30 @@ def test_stream_tails_of_every_row_count(rest):
     assert oracle.rms_rel(gr, gref) <= VJP_TOL
     assert oracle.rms_rel(a, a0) <= 2e-6
     assert oracle.rms_rel(gr, g0) <= 2e-5
+
+
+@pytest.mark.parametrize("n,side,halo_frac,masses", [(60000, 36.0, 0.8, (1e3, 1e4)), (150000, 40.0, 0.5, (1e2, 1e4)),
+                                                     (30000, 18.0, 0.9, (5e3, 2e4))])
+def test_item_shape_follows_the_work(n, side, halo_frac, masses):
+    # small clustered boxes at the default balance rule: the tiles run with items
+    # smaller than the configured 16 blocks and two windows (header words 522 and
+    # 523), and the results are the oracle's, bit for bit the same twice
+    w = synth.clustered_box(n, side, 30, 21, halo_frac=halo_frac, mass_range=masses)
+    w.mass = np.random.default_rng(3).uniform(0.5, 2.0, w.n).astype(np.float32)
+    g = synth.cotangent(w.n_active, 6)
+    announce(f"item shape n={w.n}")
+    a, gr, ok_f, ok_v = run(w, g, balance=1.0)
+    assert ok_f == 1 and ok_v == 1
+    assert_force_close(a, oracle_force(w), what="item shape")
+    assert oracle.rms_rel(gr, oracle.vjp(w.pos, w.mass, w.n_active, w.problem, g)) <= VJP_TOL
+    a0, g0, _, _ = run(w, g, (0, -1))
+    assert oracle.rms_rel(a, a0) <= 2e-6 and oracle.rms_rel(gr, g0) <= 2e-5
+    a2, g2, _, _ = run(w, g, balance=1.0)
+    assert np.array_equal(a.view(np.uint32), a2.view(np.uint32))
+    assert np.array_equal(gr.view(np.uint32), g2.view(np.uint32))
+    pos, mass = to_dev(w.pos), to_dev(w.mass)
+    ws = sr.new_workspace(sr.workspace_bytes(w.n, w.problem) + int(12.25 * 80 * w.n), DEV)
+    sr.force(pos, mass, w.problem, w.n_active, ws=ws)
+    torch.cuda.synchronize()
+    hdr = ws[4 * 518:4 * 524].view(torch.int32).tolist()
+    assert hdr[0] == 1 and 1 <= hdr[4] < 16 and 1 <= hdr[5] <= 2
