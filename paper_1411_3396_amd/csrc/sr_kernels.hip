@@ -669,19 +669,6 @@ __device__ __forceinline__ float4 fetch_pos(const Stencil &st, int v, const Src 
     return r;
 }
 
-// Pull the next work item: queues are interleaved blocks of kQueueBlock
-// items of the cost-ordered list; a wave drains the queue of its XCD first.
-// The persistent loops that call this end their bodies without a lane-0-only
-// branch: otherwise the compiler may merge that branch with this one across
-// the back edge and let the other lanes start the next item without lane 0.
-__device__ __forceinline__ int64_t next_item(uint32_t *hdr, int q, int lane, int qbase = kHdrQueue)
-{
-    uint32_t c = 0;
-    if (lane == 0) c = atomicAdd(&hdr[qbase + 32 * q], 1u);
-    c = __builtin_amdgcn_readfirstlane(c);
-    return ((int64_t)(c / kQueueBlock) * kQueues + q) * kQueueBlock + (c % kQueueBlock);
-}
-
 // Bound of a persistent loop.  A queue hands out increasing counter values,
 // so the items one wave pulls from one queue increase strictly, and no wave
 // can pull more items than exist.  A pull that breaks either rule (a loop
@@ -690,18 +677,18 @@ __device__ __forceinline__ int64_t next_item(uint32_t *hdr, int q, int lane, int
 // spinning.  limit is at most the item count; a smaller one (the host's test
 // hook) ends every wave early on purpose.  All values are wave-uniform.
 struct PullGuard {
-    int64_t limit, pulls = 0, last = -1;
+    uint32_t limit, pulls = 0, least = 0;  // least: the smallest item the next pull may return
     bool bad = false;
-    __device__ __forceinline__ explicit PullGuard(int64_t lim) : limit(lim) {}
-    __device__ __forceinline__ void next_queue() { last = -1; }
+    __device__ __forceinline__ explicit PullGuard(uint32_t lim) : limit(lim) {}
+    __device__ __forceinline__ void next_queue() { least = 0; }
     // false: leave the loop (bad is set)
-    __device__ __forceinline__ bool accept(int64_t g)
+    __device__ __forceinline__ bool accept(uint32_t g)
     {
-        if (g <= last || ++pulls > limit) {
+        if (g < least || ++pulls > limit) {
             bad = true;
             return false;
         }
-        last = g;
+        least = g + 1u;
         return true;
     }
     __device__ __forceinline__ void report(uint32_t *hdr, int lane) const
@@ -710,8 +697,61 @@ struct PullGuard {
     }
 };
 
+// The work items of one wave.  Queues are interleaved blocks of kQueueBlock
+// items of the cost-ordered list, one queue per XCD; a wave drains the queue
+// of its XCD first, then takes from the others, and asks a queue's counter
+// only while it holds items.  A list of at most as many items as waves needs
+// no counters: item w of a queue is wave w's (a longer list stays with the
+// counters throughout, since waves that become resident late would sit on
+// early, heavy items).  Adds to one counter take some 8 ns each, and thousands
+// of idle waves that each asked all eight queues cost a pass of 2,000 items 60
+// of its 95 us.
+// The persistent loops that call next() end their bodies without a lane-0-only
+// branch: otherwise the compiler may merge that branch with the one here across
+// the back edge and let the other lanes start the next item without lane 0.
+struct ItemQueue {
+    uint32_t *counters;  // queue q at counters[32 q]
+    uint32_t n;          // items (below 2^31, and so are the items a few counter steps past the end)
+    int turn = 0;        // queues done
+    bool single;         // one item per wave at most
+    PullGuard guard;
+    __device__ __forceinline__ ItemQueue(uint32_t *hdr, int qbase, uint32_t items, int64_t pull_limit)
+        : counters(hdr + qbase), n(items), single(items <= (gridDim.x & ~(unsigned)(kQueues * kQueueBlock - 1))),
+          guard((uint32_t)min((int64_t)items, pull_limit))
+    {
+    }
+    __device__ __forceinline__ int queue() const { return (int)(blockIdx.x + turn) & (kQueues - 1); }
+    __device__ __forceinline__ uint32_t item(uint32_t c) const
+    {
+        return ((c / kQueueBlock) * kQueues + queue()) * kQueueBlock + (c % kQueueBlock);
+    }
+    // the next item, wave-uniform; false when there is none (or the guard ends the loop)
+    __device__ __forceinline__ bool next(int lane, uint32_t &g)
+    {
+        if (single) {
+            if (turn > 0) return false;
+            g = item(blockIdx.x / kQueues);
+            turn = 1;
+            return g < n && guard.accept(g);
+        }
+        for (;;) {
+            uint32_t c = 0;
+            if (lane == 0) c = atomicAdd(&counters[32 * queue()], 1u);
+            g = item(__builtin_amdgcn_readfirstlane(c));
+            if (g < n) return guard.accept(g);
+            guard.next_queue();
+            for (;;) {
+                if (++turn >= kQueues) return false;
+                const uint32_t taken = __builtin_amdgcn_readfirstlane(
+                    __hip_atomic_load(&counters[32 * queue()], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                if (item(taken) < n) break;
+            }
+        }
+    }
+};
+
 // Work item with every field wave-uniform (scalar registers).
-__device__ __forceinline__ int4 load_item(const int4 *__restrict__ items, int64_t g)
+__device__ __forceinline__ int4 load_item(const int4 *__restrict__ items, uint32_t g)
 {
     const int4 it = items[g];
     return make_int4(__builtin_amdgcn_readfirstlane(it.x), __builtin_amdgcn_readfirstlane(it.y),
@@ -951,93 +991,85 @@ __device__ __forceinline__ void force_items(const Acc &acc, const int4 *__restri
 {
     const int lane = threadIdx.x;
     const float m0 = kUM ? src.m[0] : 1.0f;
-    const int64_t n_items = hdr[kHdrNItems];
-    const int q0 = blockIdx.x & (kQueues - 1);
-    PullGuard guard(min(n_items, pull_limit));
-    for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
-        const int q = (q0 + qq) & (kQueues - 1);
-        guard.next_queue();
-        for (;;) {
-            const int64_t g = next_item(hdr, q, lane);
-            if (g >= n_items || !guard.accept(g)) break;
-            const int4 it = load_item(items, g);
-            const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
-            const SegParams &S = acc.get(item_seg(it.w));
-            const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
-            float cq[6];
+    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit);
+    for (uint32_t g; queue.next(lane, g);) {
+        const int4 it = load_item(items, g);
+        const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
+        const SegParams &S = acc.get(item_seg(it.w));
+        const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
+        float cq[6];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) cq[k] = S.pc.q[k];
-            cq[5] = keep_in_vgpr(cq[5]);
-            Stencil st;
-            stencil_setup(S, it.x, start, nact, false, lane, st, item_nd(it.w));
-            auto fetch_p = [&](int v, float4 &c0, float4 &) { c0 = fetch_pos(st, v, src); };
-            if (item_two(it.w)) {
-                const bool va = lane < nt, vb = kWave + lane < nt;
-                float pax = 0.f, pay = 0.f, paz = 0.f, pbx = 0.f, pby = 0.f, pbz = 0.f;
-                if (va) {
-                    pax = src.x[t0 + lane];
-                    pay = src.y[t0 + lane];
-                    paz = src.z[t0 + lane];
-                }
-                if (vb) {
-                    pbx = src.x[t0 + kWave + lane];
-                    pby = src.y[t0 + kWave + lane];
-                    pbz = src.z[t0 + kWave + lane];
-                }
-                const Box box = target_box(va, pax, pay, paz, vb, pbx, pby, pbz);
-                float aax = 0.f, aay = 0.f, aaz = 0.f, abx = 0.f, aby = 0.f, abz = 0.f;
-                stream_sources<1, kStageForce>(st, box, cull2, lane, stage, stage, fetch_p, [&](int n) {
-                    const int n4 = (n + 3) >> 2;
-                    for (int u = 0; u < n4; ++u) {
-#pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) {
-                            const float4 sj = stage[4 * u + q4];
-                            force_pair<kSoft, kUM>(sj, pax, pay, paz, eps2, tc2, cq, aax, aay, aaz);
-                            force_pair<kSoft, kUM>(sj, pbx, pby, pbz, eps2, tc2, cq, abx, aby, abz);
-                        }
-                    }
-                });
-                if (va) store3(out, n_out, out_row[t0 + lane], m0 * aax, m0 * aay, m0 * aaz);
-                if (vb) store3(out, n_out, out_row[t0 + kWave + lane], m0 * abx, m0 * aby, m0 * abz);
-                continue;
+        for (int k = 0; k < 6; ++k) cq[k] = S.pc.q[k];
+        cq[5] = keep_in_vgpr(cq[5]);
+        Stencil st;
+        stencil_setup(S, it.x, start, nact, false, lane, st, item_nd(it.w));
+        auto fetch_p = [&](int v, float4 &c0, float4 &) { c0 = fetch_pos(st, v, src); };
+        if (item_two(it.w)) {
+            const bool va = lane < nt, vb = kWave + lane < nt;
+            float pax = 0.f, pay = 0.f, paz = 0.f, pbx = 0.f, pby = 0.f, pbz = 0.f;
+            if (va) {
+                pax = src.x[t0 + lane];
+                pay = src.y[t0 + lane];
+                paz = src.z[t0 + lane];
             }
-            const int kl = 1 << lk;
-            const int t = lane >> lk, sub = lane & (kl - 1);
-            const bool tv = t < nt;
-            float px = 0.f, py = 0.f, pz = 0.f;
-            if (tv) {
-                px = src.x[t0 + t];
-                py = src.y[t0 + t];
-                pz = src.z[t0 + t];
+            if (vb) {
+                pbx = src.x[t0 + kWave + lane];
+                pby = src.y[t0 + kWave + lane];
+                pbz = src.z[t0 + kWave + lane];
             }
-            const Box box = target_box(tv, px, py, pz, false, 0.f, 0.f, 0.f);
-            float ax = 0.f, ay = 0.f, az = 0.f;
+            const Box box = target_box(va, pax, pay, paz, vb, pbx, pby, pbz);
+            float aax = 0.f, aay = 0.f, aaz = 0.f, abx = 0.f, aby = 0.f, abz = 0.f;
             stream_sources<1, kStageForce>(st, box, cull2, lane, stage, stage, fetch_p, [&](int n) {
-                if (lk == 0) {
-                    const int n8 = (n + 7) >> 3;
-                    for (int u = 0; u < n8; ++u) {
+                const int n4 = (n + 3) >> 2;
+                for (int u = 0; u < n4; ++u) {
 #pragma unroll
-                        for (int q8 = 0; q8 < 8; ++q8)
-                            force_pair<kSoft, kUM>(stage[8 * u + q8], px, py, pz, eps2, tc2, cq, ax, ay, az);
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const float4 sj = stage[4 * u + q4];
+                        force_pair<kSoft, kUM>(sj, pax, pay, paz, eps2, tc2, cq, aax, aay, aaz);
+                        force_pair<kSoft, kUM>(sj, pbx, pby, pbz, eps2, tc2, cq, abx, aby, abz);
                     }
-                } else {
-                    const int niter = (n + kl - 1) >> lk;
-#pragma unroll 2
-                    for (int i = 0; i < niter; ++i)
-                        force_pair<kSoft, kUM>(stage[sub + (i << lk)], px, py, pz, eps2, tc2, cq, ax, ay, az);
                 }
             });
-            for (int o = 1; o < kl; o <<= 1) {
-                ax += __shfl_xor(ax, o);
-                ay += __shfl_xor(ay, o);
-                az += __shfl_xor(az, o);
-            }
-            // every lane of a target's group holds the same sum: all store it, so the
-            // loop body ends without a single-lane branch (see next_item)
-            if (tv) store3(out, n_out, out_row[t0 + t], m0 * ax, m0 * ay, m0 * az);
+            if (va) store3(out, n_out, out_row[t0 + lane], m0 * aax, m0 * aay, m0 * aaz);
+            if (vb) store3(out, n_out, out_row[t0 + kWave + lane], m0 * abx, m0 * aby, m0 * abz);
+            continue;
         }
+        const int kl = 1 << lk;
+        const int t = lane >> lk, sub = lane & (kl - 1);
+        const bool tv = t < nt;
+        float px = 0.f, py = 0.f, pz = 0.f;
+        if (tv) {
+            px = src.x[t0 + t];
+            py = src.y[t0 + t];
+            pz = src.z[t0 + t];
+        }
+        const Box box = target_box(tv, px, py, pz, false, 0.f, 0.f, 0.f);
+        float ax = 0.f, ay = 0.f, az = 0.f;
+        stream_sources<1, kStageForce>(st, box, cull2, lane, stage, stage, fetch_p, [&](int n) {
+            if (lk == 0) {
+                const int n8 = (n + 7) >> 3;
+                for (int u = 0; u < n8; ++u) {
+#pragma unroll
+                    for (int q8 = 0; q8 < 8; ++q8)
+                        force_pair<kSoft, kUM>(stage[8 * u + q8], px, py, pz, eps2, tc2, cq, ax, ay, az);
+                }
+            } else {
+                const int niter = (n + kl - 1) >> lk;
+#pragma unroll 2
+                for (int i = 0; i < niter; ++i)
+                    force_pair<kSoft, kUM>(stage[sub + (i << lk)], px, py, pz, eps2, tc2, cq, ax, ay, az);
+            }
+        });
+        for (int o = 1; o < kl; o <<= 1) {
+            ax += __shfl_xor(ax, o);
+            ay += __shfl_xor(ay, o);
+            az += __shfl_xor(az, o);
+        }
+        // every lane of a target's group holds the same sum: all store it, so the
+        // loop body ends without a single-lane branch (see ItemQueue)
+        if (tv) store3(out, n_out, out_row[t0 + t], m0 * ax, m0 * ay, m0 * az);
     }
-    guard.report(hdr, lane);
+    queue.guard.report(hdr, lane);
 }
 
 template <class Acc, bool kSoft, int kOcc>
@@ -1072,106 +1104,98 @@ __device__ __forceinline__ void vjp_items(const Acc &acc, const int4 *__restrict
     const int lane = threadIdx.x;
     // the common mass (or 1), times -3: the pair sums are at the scale -1/3
     const float m0 = -3.0f * (kUM ? src.m[0] : 1.0f);
-    const int64_t n_items = hdr[kHdrNItems];
-    const int q0 = blockIdx.x & (kQueues - 1);
-    PullGuard guard(min(n_items, pull_limit));
-    for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
-        const int q = (q0 + qq) & (kQueues - 1);
-        guard.next_queue();
-        for (;;) {
-            const int64_t g = next_item(hdr, q, lane);
-            if (g >= n_items || !guard.accept(g)) break;
-            const int4 it = load_item(items, g);
-            const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
-            const SegParams &S = acc.get(item_seg(it.w));
-            const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
-            float cq[6], cd[5];
+    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit);
+    for (uint32_t g; queue.next(lane, g);) {
+        const int4 it = load_item(items, g);
+        const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
+        const SegParams &S = acc.get(item_seg(it.w));
+        const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
+        float cq[6], cd[5];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) cq[k] = S.pc.qa[k];
-            cq[5] = keep_in_vgpr(cq[5]);
+        for (int k = 0; k < 6; ++k) cq[k] = S.pc.qa[k];
+        cq[5] = keep_in_vgpr(cq[5]);
 #pragma unroll
-            for (int k = 0; k < 5; ++k) cd[k] = S.pc.dqa[k];
-            Stencil st;
-            stencil_setup(S, it.x, start, nact, item_psrc(it.w), lane, st, item_nd(it.w));
-            auto fetch_pg = [&](int v, float4 &c0, float4 &c1) {
-                fetch_vjp(st, v, src, gx, gy, gz, c0, c1);
-            };
-            if (item_two(it.w)) {
-                const int ba = t0 + lane, bb = t0 + kWave + lane;
-                const bool va = lane < nt, vb = kWave + lane < nt;
-                float pax = 0.f, pay = 0.f, paz = 0.f, ma = 0.f, gax = 0.f, gay = 0.f, gaz = 0.f;
-                float pbx = 0.f, pby = 0.f, pbz = 0.f, mb = 0.f, gbx = 0.f, gby = 0.f, gbz = 0.f;
-                if (va) {
-                    pax = src.x[ba]; pay = src.y[ba]; paz = src.z[ba]; ma = src.m[ba];
-                    gax = gx[ba]; gay = gy[ba]; gaz = gz[ba];
-                }
-                if (vb) {
-                    pbx = src.x[bb]; pby = src.y[bb]; pbz = src.z[bb]; mb = src.m[bb];
-                    gbx = gx[bb]; gby = gy[bb]; gbz = gz[bb];
-                }
-                const Box box = target_box(va, pax, pay, paz, vb, pbx, pby, pbz);
-                float rax = 0.f, ray = 0.f, raz = 0.f, rbx = 0.f, rby = 0.f, rbz = 0.f;
-                stream_sources<2, kStageVjp>(st, box, cull2, lane, stage_p, stage_g, fetch_pg, [&](int n) {
-                    const int n2 = (n + 1) >> 1;
-                    for (int u = 0; u < n2; ++u) {
-#pragma unroll
-                        for (int q2 = 0; q2 < 2; ++q2) {
-                            const float4 sp = stage_p[2 * u + q2];
-                            const float4 sg = stage_g[2 * u + q2];
-                            vjp_pair<kSoft, kUM>(sp, sg, pax, pay, paz, ma, gax, gay, gaz, eps2, tc2, cq,
-                                            cd, rax, ray, raz);
-                            vjp_pair<kSoft, kUM>(sp, sg, pbx, pby, pbz, mb, gbx, gby, gbz, eps2, tc2, cq,
-                                            cd, rbx, rby, rbz);
-                        }
-                    }
-                });
-                if (va) store3(out, n_out, perm[ba], m0 * rax, m0 * ray, m0 * raz);
-                if (vb) store3(out, n_out, perm[bb], m0 * rbx, m0 * rby, m0 * rbz);
-                continue;
+        for (int k = 0; k < 5; ++k) cd[k] = S.pc.dqa[k];
+        Stencil st;
+        stencil_setup(S, it.x, start, nact, item_psrc(it.w), lane, st, item_nd(it.w));
+        auto fetch_pg = [&](int v, float4 &c0, float4 &c1) {
+            fetch_vjp(st, v, src, gx, gy, gz, c0, c1);
+        };
+        if (item_two(it.w)) {
+            const int ba = t0 + lane, bb = t0 + kWave + lane;
+            const bool va = lane < nt, vb = kWave + lane < nt;
+            float pax = 0.f, pay = 0.f, paz = 0.f, ma = 0.f, gax = 0.f, gay = 0.f, gaz = 0.f;
+            float pbx = 0.f, pby = 0.f, pbz = 0.f, mb = 0.f, gbx = 0.f, gby = 0.f, gbz = 0.f;
+            if (va) {
+                pax = src.x[ba]; pay = src.y[ba]; paz = src.z[ba]; ma = src.m[ba];
+                gax = gx[ba]; gay = gy[ba]; gaz = gz[ba];
             }
-            const int kl = 1 << lk;
-            const int t = lane >> lk, sub = lane & (kl - 1);
-            const bool tv = t < nt;
-            float px = 0.f, py = 0.f, pz = 0.f, mk = 0.f, gkx = 0.f, gky = 0.f, gkz = 0.f;
-            if (tv) {
-                const int b = t0 + t;
-                px = src.x[b];
-                py = src.y[b];
-                pz = src.z[b];
-                mk = src.m[b];
-                gkx = gx[b];
-                gky = gy[b];
-                gkz = gz[b];
+            if (vb) {
+                pbx = src.x[bb]; pby = src.y[bb]; pbz = src.z[bb]; mb = src.m[bb];
+                gbx = gx[bb]; gby = gy[bb]; gbz = gz[bb];
             }
-            const Box box = target_box(tv, px, py, pz, false, 0.f, 0.f, 0.f);
-            float rx = 0.f, ry = 0.f, rz = 0.f;
+            const Box box = target_box(va, pax, pay, paz, vb, pbx, pby, pbz);
+            float rax = 0.f, ray = 0.f, raz = 0.f, rbx = 0.f, rby = 0.f, rbz = 0.f;
             stream_sources<2, kStageVjp>(st, box, cull2, lane, stage_p, stage_g, fetch_pg, [&](int n) {
-                if (lk == 0) {
-                    const int n4 = (n + 3) >> 2;
-                    for (int u = 0; u < n4; ++u) {
+                const int n2 = (n + 1) >> 1;
+                for (int u = 0; u < n2; ++u) {
 #pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4)
-                            vjp_pair<kSoft, kUM>(stage_p[4 * u + q4], stage_g[4 * u + q4], px, py, pz, mk,
-                                            gkx, gky, gkz, eps2, tc2, cq, cd, rx, ry, rz);
-                    }
-                } else {
-                    const int niter = (n + kl - 1) >> lk;
-                    for (int i = 0; i < niter; ++i) {
-                        const int e = sub + (i << lk);
-                        vjp_pair<kSoft, kUM>(stage_p[e], stage_g[e], px, py, pz, mk, gkx, gky, gkz, eps2,
-                                        tc2, cq, cd, rx, ry, rz);
+                    for (int q2 = 0; q2 < 2; ++q2) {
+                        const float4 sp = stage_p[2 * u + q2];
+                        const float4 sg = stage_g[2 * u + q2];
+                        vjp_pair<kSoft, kUM>(sp, sg, pax, pay, paz, ma, gax, gay, gaz, eps2, tc2, cq,
+                                        cd, rax, ray, raz);
+                        vjp_pair<kSoft, kUM>(sp, sg, pbx, pby, pbz, mb, gbx, gby, gbz, eps2, tc2, cq,
+                                        cd, rbx, rby, rbz);
                     }
                 }
             });
-            for (int o = 1; o < kl; o <<= 1) {
-                rx += __shfl_xor(rx, o);
-                ry += __shfl_xor(ry, o);
-                rz += __shfl_xor(rz, o);
-            }
-            if (tv) store3(out, n_out, perm[t0 + t], m0 * rx, m0 * ry, m0 * rz);
+            if (va) store3(out, n_out, perm[ba], m0 * rax, m0 * ray, m0 * raz);
+            if (vb) store3(out, n_out, perm[bb], m0 * rbx, m0 * rby, m0 * rbz);
+            continue;
         }
+        const int kl = 1 << lk;
+        const int t = lane >> lk, sub = lane & (kl - 1);
+        const bool tv = t < nt;
+        float px = 0.f, py = 0.f, pz = 0.f, mk = 0.f, gkx = 0.f, gky = 0.f, gkz = 0.f;
+        if (tv) {
+            const int b = t0 + t;
+            px = src.x[b];
+            py = src.y[b];
+            pz = src.z[b];
+            mk = src.m[b];
+            gkx = gx[b];
+            gky = gy[b];
+            gkz = gz[b];
+        }
+        const Box box = target_box(tv, px, py, pz, false, 0.f, 0.f, 0.f);
+        float rx = 0.f, ry = 0.f, rz = 0.f;
+        stream_sources<2, kStageVjp>(st, box, cull2, lane, stage_p, stage_g, fetch_pg, [&](int n) {
+            if (lk == 0) {
+                const int n4 = (n + 3) >> 2;
+                for (int u = 0; u < n4; ++u) {
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        vjp_pair<kSoft, kUM>(stage_p[4 * u + q4], stage_g[4 * u + q4], px, py, pz, mk,
+                                        gkx, gky, gkz, eps2, tc2, cq, cd, rx, ry, rz);
+                }
+            } else {
+                const int niter = (n + kl - 1) >> lk;
+                for (int i = 0; i < niter; ++i) {
+                    const int e = sub + (i << lk);
+                    vjp_pair<kSoft, kUM>(stage_p[e], stage_g[e], px, py, pz, mk, gkx, gky, gkz, eps2,
+                                    tc2, cq, cd, rx, ry, rz);
+                }
+            }
+        });
+        for (int o = 1; o < kl; o <<= 1) {
+            rx += __shfl_xor(rx, o);
+            ry += __shfl_xor(ry, o);
+            rz += __shfl_xor(rz, o);
+        }
+        if (tv) store3(out, n_out, perm[t0 + t], m0 * rx, m0 * ry, m0 * rz);
     }
-    guard.report(hdr, lane);
+    queue.guard.report(hdr, lane);
 }
 
 template <class Acc, bool kSoft, int kOcc>
@@ -1203,52 +1227,45 @@ __global__ __launch_bounds__(64) void k_count(Acc acc, const int4 *__restrict__ 
 {
     __shared__ float4 stage[kWave];
     const int lane = threadIdx.x;
-    const int64_t n_items = hdr[kHdrNItems];
-    const int q0 = blockIdx.x & (kQueues - 1);
+    const uint32_t n_items = hdr[kHdrNItems];
     unsigned long long pairs = 0;
-    PullGuard guard(min(n_items, pull_limit));
-    for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
-        const int q = (q0 + qq) & (kQueues - 1);
-        guard.next_queue();
-        for (;;) {
-            const int64_t g = next_item(hdr, q, lane);
-            if (g >= n_items || !guard.accept(g)) break;
-            const int4 it = load_item(items, g);
-            const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
-            const SegParams &S = acc.get(item_seg(it.w));
-            const float eps2 = S.pc.eps2, tc2 = S.pc.tc2;
-            Stencil st;
-            stencil_setup(S, it.x, start, nact, item_psrc(it.w), lane, st);
-            const int kl = 1 << lk;
-            const int t = lane >> lk, sub = lane & (kl - 1);
-            const bool tv = t < nt;
-            float px = 0.f, py = 0.f, pz = 0.f;
-            if (tv) {
-                px = src.x[t0 + t];
-                py = src.y[t0 + t];
-                pz = src.z[t0 + t];
-            }
-            unsigned cnt_lane = 0;
-            float4 nxt = fetch_pos(st, lane, src);
-            for (int base = 0; base < st.total; base += kWave) {
-                __syncthreads();
-                stage[lane] = nxt;
-                __syncthreads();
-                if (base + kWave < st.total) nxt = fetch_pos(st, base + kWave + lane, src);
-                const int cnt = min(kWave, st.total - base);
-                const int niter = (cnt + kl - 1) >> lk;
-                for (int i = 0; i < niter; ++i) {
-                    const float4 s = stage[sub + (i << lk)];
-                    const float dx = s.x - px, dy = s.y - py, dz = s.z - pz;
-                    const float tt = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
-                    const float s2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    cnt_lane += (tt < tc2 && s2 > 0.f) ? 1u : 0u;
-                }
-            }
-            if (tv) pairs += cnt_lane;
+    ItemQueue queue(hdr, kHdrQueue, n_items, pull_limit);
+    for (uint32_t g; queue.next(lane, g);) {
+        const int4 it = load_item(items, g);
+        const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
+        const SegParams &S = acc.get(item_seg(it.w));
+        const float eps2 = S.pc.eps2, tc2 = S.pc.tc2;
+        Stencil st;
+        stencil_setup(S, it.x, start, nact, item_psrc(it.w), lane, st);
+        const int kl = 1 << lk;
+        const int t = lane >> lk, sub = lane & (kl - 1);
+        const bool tv = t < nt;
+        float px = 0.f, py = 0.f, pz = 0.f;
+        if (tv) {
+            px = src.x[t0 + t];
+            py = src.y[t0 + t];
+            pz = src.z[t0 + t];
         }
+        unsigned cnt_lane = 0;
+        float4 nxt = fetch_pos(st, lane, src);
+        for (int base = 0; base < st.total; base += kWave) {
+            __syncthreads();
+            stage[lane] = nxt;
+            __syncthreads();
+            if (base + kWave < st.total) nxt = fetch_pos(st, base + kWave + lane, src);
+            const int cnt = min(kWave, st.total - base);
+            const int niter = (cnt + kl - 1) >> lk;
+            for (int i = 0; i < niter; ++i) {
+                const float4 s = stage[sub + (i << lk)];
+                const float dx = s.x - px, dy = s.y - py, dz = s.z - pz;
+                const float tt = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
+                const float s2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                cnt_lane += (tt < tc2 && s2 > 0.f) ? 1u : 0u;
+            }
+        }
+        if (tv) pairs += cnt_lane;
     }
-    guard.report(hdr, lane);
+    queue.guard.report(hdr, lane);
     for (int o = 32; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o);
     if (lane == 0 && pairs)
         atomicAdd((unsigned long long *)&hdr[kHdrPairs], pairs);
@@ -2025,160 +2042,153 @@ __device__ __forceinline__ void force_sym_items(const Acc &acc, const int4 *__re
                                                 int *tix, SymRed<kW> &red, int64_t pull_limit)
 {
     const int lane = threadIdx.x;
-    const int64_t n_items = hdr[kHdrSymNItems];
+    const uint32_t n_items = hdr[kHdrSymNItems];
     // tiles off (or nothing to do): leave before touching the queues, which
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
     const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
-    const int q0 = blockIdx.x & (kQueues - 1);
-    PullGuard guard(min(n_items, pull_limit));
-    for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
-        const int q = (q0 + qq) & (kQueues - 1);
-        guard.next_queue();
-        for (;;) {
-            const int64_t gi = next_item(hdr, q, lane, kHdrSymQueue);
-            if (gi >= n_items || !guard.accept(gi)) break;
-            const int4 it = load_item(items, gi);
-            const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
-            const SegParams &S = acc.get(it.w);
-            const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
-            float cq[6];
+    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit);
+    for (uint32_t gi; queue.next(lane, gi);) {
+        const int4 it = load_item(items, gi);
+        const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
+        const SegParams &S = acc.get(it.w);
+        const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
+        float cq[6];
 #pragma unroll
-            for (int i = 0; i < 6; ++i) cq[i] = S.pc.q[i];
-            cq[5] = keep_in_vgpr(cq[5]);
-            SymStencil st;
-            sym_stencil_setup(S, c, start, nact, sym_base, sym_pref, lane, st);
-            const int D = __shfl(st.cnt, 0);  // segment 0 is the cell itself
-            const int c0s = start[c];
-            const int tbase = sym_base[c] + kk * D;  // group 0: the target slots
-            const int p0 = g * K, p1 = min(p0 + K, D / kWave);
-            const int k_end = min((kk + 1) * R, (st.total + kW - 1) / kW);
-            // the group's windows in turn: the first stores each block's target sums
-            // to its slot, the next ones add to it (this wave alone writes the slot)
-            for (int k = kk * R; k < k_end; ++k) {
-                const bool first = k == kk * R;
-                const int w0 = k * kW, w1 = min(w0 + kW, st.total);
-                for (int i = lane; i < kW; i += kWave) red.x[i] = red.y[i] = red.z[i] = 0.f;
-                auto fetch_p = [&](int v, float4 &a, float4 &) {
+        for (int i = 0; i < 6; ++i) cq[i] = S.pc.q[i];
+        cq[5] = keep_in_vgpr(cq[5]);
+        SymStencil st;
+        sym_stencil_setup(S, c, start, nact, sym_base, sym_pref, lane, st);
+        const int D = __shfl(st.cnt, 0);  // segment 0 is the cell itself
+        const int c0s = start[c];
+        const int tbase = sym_base[c] + kk * D;  // group 0: the target slots
+        const int p0 = g * K, p1 = min(p0 + K, D / kWave);
+        const int k_end = min((kk + 1) * R, (st.total + kW - 1) / kW);
+        // the group's windows in turn: the first stores each block's target sums
+        // to its slot, the next ones add to it (this wave alone writes the slot)
+        for (int k = kk * R; k < k_end; ++k) {
+            const bool first = k == kk * R;
+            const int w0 = k * kW, w1 = min(w0 + kW, st.total);
+            for (int i = lane; i < kW; i += kWave) red.x[i] = red.y[i] = red.z[i] = 0.f;
+            auto fetch_p = [&](int v, float4 &a, float4 &) {
+                int slot;
+                a = sym_fetch_pos(st, v, w1, src, slot);
+            };
+            // windows of 256: the window's sources once, held in registers for all blocks
+            constexpr int kHeld = kW == 256 ? kW / kWave : 1;
+            float4 held[kHeld];
+#pragma unroll
+            for (int i = 0; i < kHeld; ++i) {
+                held[i] = make_float4(kFar, kFar, kFar, 0.f);
+                if (kW == 256 && w0 + i * kWave < w1) {
                     int slot;
-                    a = sym_fetch_pos(st, v, w1, src, slot);
-                };
-                // windows of 256: the window's sources once, held in registers for all blocks
-                constexpr int kHeld = kW == 256 ? kW / kWave : 1;
-                float4 held[kHeld];
-#pragma unroll
-                for (int i = 0; i < kHeld; ++i) {
-                    held[i] = make_float4(kFar, kFar, kFar, 0.f);
-                    if (kW == 256 && w0 + i * kWave < w1) {
-                        int slot;
-                        held[i] = sym_fetch_pos(st, w0 + i * kWave + lane, w1, src, slot);
-                    }
+                    held[i] = sym_fetch_pos(st, w0 + i * kWave + lane, w1, src, slot);
                 }
-                for (int p = p0; p < p1; ++p) {
-                    const int b = c0s + p * kWave + lane;
-                    const float px = src.x[b], py = src.y[b], pz = src.z[b];
-                    const float mi = kUM ? 1.f : src.m[b];
-                    const Box box = target_box(true, px, py, pz, false, 0.f, 0.f, 0.f);
-                    float ax = 0.f, ay = 0.f, az = 0.f;
-                    if (p * kWave >= w0 && p * kWave < w1) {
-                        // the block against itself: steps 1..32, the last one on half the lanes
-                        __syncthreads();
-                        tile[lane] = make_float4(px, py, pz, src.m[b]);
-                        tile[lane + kWave] = tile[lane];
-                        __syncthreads();
-                        float bx = 0.f, by = 0.f, bz = 0.f;
-                        for (int s = 1; s <= kWave / 2; ++s) {
-                            float4 sj = tile[lane + s];
-                            if (s == kWave / 2 && lane >= kWave / 2) sj = make_float4(kFar, kFar, kFar, 0.f);
-                            sym_force_step<kSoft, kUM>(sj, px, py, pz, mi, eps2, tc2, cq, ax, ay, az, bx, by, bz);
+            }
+            for (int p = p0; p < p1; ++p) {
+                const int b = c0s + p * kWave + lane;
+                const float px = src.x[b], py = src.y[b], pz = src.z[b];
+                const float mi = kUM ? 1.f : src.m[b];
+                const Box box = target_box(true, px, py, pz, false, 0.f, 0.f, 0.f);
+                float ax = 0.f, ay = 0.f, az = 0.f;
+                if (p * kWave >= w0 && p * kWave < w1) {
+                    // the block against itself: steps 1..32, the last one on half the lanes
+                    __syncthreads();
+                    tile[lane] = make_float4(px, py, pz, src.m[b]);
+                    tile[lane + kWave] = tile[lane];
+                    __syncthreads();
+                    float bx = 0.f, by = 0.f, bz = 0.f;
+                    for (int s = 1; s <= kWave / 2; ++s) {
+                        float4 sj = tile[lane + s];
+                        if (s == kWave / 2 && lane >= kWave / 2) sj = make_float4(kFar, kFar, kFar, 0.f);
+                        sym_force_step<kSoft, kUM>(sj, px, py, pz, mi, eps2, tc2, cq, ax, ay, az, bx, by, bz);
+                        bx = rotate_down(bx);
+                        by = rotate_down(by);
+                        bz = rotate_down(bz);
+                    }
+                    const int r = p * kWave - w0 + ((lane + kWave / 2 + 1) & (kWave - 1));
+                    red.x[r] += bx;
+                    red.y[r] += by;
+                    red.z[r] += bz;
+                }
+                const int vs = max(w0, (p + 1) * kWave);
+                auto tile_fn = [&](int my) {
+                    float bx = 0.f, by = 0.f, bz = 0.f;
+                    const float4 *t = tile + lane;
+                    for (int s = 0; s < kWave; s += 8) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            sym_force_step<kSoft, kUM>(t[s + u], px, py, pz, mi, eps2, tc2, cq, ax, ay, az,
+                                                       bx, by, bz);
                             bx = rotate_down(bx);
                             by = rotate_down(by);
                             bz = rotate_down(bz);
                         }
-                        const int r = p * kWave - w0 + ((lane + kWave / 2 + 1) & (kWave - 1));
-                        red.x[r] += bx;
-                        red.y[r] += by;
-                        red.z[r] += bz;
                     }
-                    const int vs = max(w0, (p + 1) * kWave);
-                    auto tile_fn = [&](int my) {
+                    if (my >= 0) {
+                        red.x[my] += bx;
+                        red.y[my] += by;
+                        red.z[my] += bz;
+                    }
+                };
+                auto rows_fn = [&](int chunks) {
+                    const float4 *t = tile + kWave + (lane & 15);
+                    for (int k = 0; k < chunks; ++k) {
+                        row_chunk(tile, k, lane);
                         float bx = 0.f, by = 0.f, bz = 0.f;
-                        const float4 *t = tile + lane;
-                        for (int s = 0; s < kWave; s += 8) {
+                        for (int s = 0; s < 16; s += 8) {
 #pragma unroll
                             for (int u = 0; u < 8; ++u) {
-                                sym_force_step<kSoft, kUM>(t[s + u], px, py, pz, mi, eps2, tc2, cq, ax, ay, az,
-                                                           bx, by, bz);
-                                bx = rotate_down(bx);
-                                by = rotate_down(by);
-                                bz = rotate_down(bz);
+                                sym_force_step<kSoft, kUM>(t[s + u], px, py, pz, mi, eps2, tc2, cq, ax, ay,
+                                                           az, bx, by, bz);
+                                bx = rotate_row(bx);
+                                by = rotate_row(by);
+                                bz = rotate_row(bz);
                             }
                         }
-                        if (my >= 0) {
+                        bx = sum_rows(bx);
+                        by = sum_rows(by);
+                        bz = sum_rows(bz);
+                        const int my = tix[16 * k + (lane & 15)];
+                        if (lane < 16 && my >= 0) {
                             red.x[my] += bx;
                             red.y[my] += by;
                             red.z[my] += bz;
                         }
-                    };
-                    auto rows_fn = [&](int chunks) {
-                        const float4 *t = tile + kWave + (lane & 15);
-                        for (int k = 0; k < chunks; ++k) {
-                            row_chunk(tile, k, lane);
-                            float bx = 0.f, by = 0.f, bz = 0.f;
-                            for (int s = 0; s < 16; s += 8) {
-#pragma unroll
-                                for (int u = 0; u < 8; ++u) {
-                                    sym_force_step<kSoft, kUM>(t[s + u], px, py, pz, mi, eps2, tc2, cq, ax, ay,
-                                                               az, bx, by, bz);
-                                    bx = rotate_row(bx);
-                                    by = rotate_row(by);
-                                    bz = rotate_row(bz);
-                                }
-                            }
-                            bx = sum_rows(bx);
-                            by = sum_rows(by);
-                            bz = sum_rows(bz);
-                            const int my = tix[16 * k + (lane & 15)];
-                            if (lane < 16 && my >= 0) {
-                                red.x[my] += bx;
-                                red.y[my] += by;
-                                red.z[my] += bz;
-                            }
-                        }
-                    };
-                    if constexpr (kW == 256)
-                        sym_stream_held(held, vs, w1, w0, box, cull2, lane, tile, tix, tile_fn, rows_fn);
-                    else
-                        sym_stream<1>(vs, w1, w0, box, cull2, lane, tile, tile, tix, fetch_p, tile_fn, rows_fn);
-                    const int64_t o = 3 * ((int64_t)tbase + p * kWave + lane);
-                    if (first) {
-                        pool[o] = ax;
-                        pool[o + 1] = ay;
-                        pool[o + 2] = az;
-                    } else {
-                        pool[o] += ax;
-                        pool[o + 1] += ay;
-                        pool[o + 2] += az;
                     }
+                };
+                if constexpr (kW == 256)
+                    sym_stream_held(held, vs, w1, w0, box, cull2, lane, tile, tix, tile_fn, rows_fn);
+                else
+                    sym_stream<1>(vs, w1, w0, box, cull2, lane, tile, tile, tix, fetch_p, tile_fn, rows_fn);
+                const int64_t o = 3 * ((int64_t)tbase + p * kWave + lane);
+                if (first) {
+                    pool[o] = ax;
+                    pool[o + 1] = ay;
+                    pool[o + 2] = az;
+                } else {
+                    pool[o] += ax;
+                    pool[o + 1] += ay;
+                    pool[o + 2] += az;
                 }
-                __syncthreads();
-                // the window's opposite sums to their source slots
-                for (int i = 0; i < w1 - w0; i += kWave) {
-                    const int v = w0 + i + lane;
-                    const int q = sym_locate(st, v);
-                    const int64_t slot = (int64_t)__shfl(st.sbase, q) + (int64_t)g * __shfl(st.cnt, q) +
-                                         (min(v, st.total - 1) - __shfl(st.excl, q));
-                    if (v < w1) {
-                        pool[3 * slot] = red.x[i + lane];
-                        pool[3 * slot + 1] = red.y[i + lane];
-                        pool[3 * slot + 2] = red.z[i + lane];
-                    }
-                }
-                __syncthreads();
             }
+            __syncthreads();
+            // the window's opposite sums to their source slots
+            for (int i = 0; i < w1 - w0; i += kWave) {
+                const int v = w0 + i + lane;
+                const int q = sym_locate(st, v);
+                const int64_t slot = (int64_t)__shfl(st.sbase, q) + (int64_t)g * __shfl(st.cnt, q) +
+                                     (min(v, st.total - 1) - __shfl(st.excl, q));
+                if (v < w1) {
+                    pool[3 * slot] = red.x[i + lane];
+                    pool[3 * slot + 1] = red.y[i + lane];
+                    pool[3 * slot + 2] = red.z[i + lane];
+                }
+            }
+            __syncthreads();
         }
     }
-    guard.report(hdr, lane);
+    queue.guard.report(hdr, lane);
 }
 
 template <class Acc, bool kSoft, int kW, int kOcc>
@@ -2214,161 +2224,154 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
                                               SymRed<kW> &red, int64_t pull_limit)
 {
     const int lane = threadIdx.x;
-    const int64_t n_items = hdr[kHdrSymNItems];
+    const uint32_t n_items = hdr[kHdrSymNItems];
     // tiles off (or nothing to do): leave before touching the queues, which
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
     const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
-    const int q0 = blockIdx.x & (kQueues - 1);
-    PullGuard guard(min(n_items, pull_limit));
-    for (int qq = 0; qq < kQueues && !guard.bad; ++qq) {
-        const int q = (q0 + qq) & (kQueues - 1);
-        guard.next_queue();
-        for (;;) {
-            const int64_t gi = next_item(hdr, q, lane, kHdrSymQueue);
-            if (gi >= n_items || !guard.accept(gi)) break;
-            const int4 it = load_item(items, gi);
-            const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
-            const SegParams &S = acc.get(it.w);
-            const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
-            float cq[6], cd[5];
+    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit);
+    for (uint32_t gi; queue.next(lane, gi);) {
+        const int4 it = load_item(items, gi);
+        const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
+        const SegParams &S = acc.get(it.w);
+        const float eps2 = S.pc.eps2, tc2 = S.pc.tc2, cull2 = S.pc.cull2;
+        float cq[6], cd[5];
 #pragma unroll
-            for (int i = 0; i < 6; ++i) cq[i] = S.pc.qa[i];
-            cq[5] = keep_in_vgpr(cq[5]);
+        for (int i = 0; i < 6; ++i) cq[i] = S.pc.qa[i];
+        cq[5] = keep_in_vgpr(cq[5]);
 #pragma unroll
-            for (int i = 0; i < 5; ++i) cd[i] = S.pc.dqa[i];
-            cd[4] = keep_in_vgpr(cd[4]);
-            SymStencil st;
-            sym_stencil_setup(S, c, start, nact, sym_base, sym_pref, lane, st);
-            const int D = __shfl(st.cnt, 0);
-            const int c0s = start[c];
-            const int tbase = sym_base[c] + kk * D;  // group 0: the target slots
-            const int p0 = g * K, p1 = min(p0 + K, D / kWave);
-            const int k_end = min((kk + 1) * R, (st.total + kW - 1) / kW);
-            // the group's windows in turn: the first stores each block's target sums
-            // to its slot, the next ones add to it (this wave alone writes the slot)
-            for (int k = kk * R; k < k_end; ++k) {
-                const bool first = k == kk * R;
-                const int w0 = k * kW, w1 = min(w0 + kW, st.total);
-                for (int i = lane; i < kW; i += kWave) red.x[i] = red.y[i] = red.z[i] = 0.f;
-                auto fetch_pg = [&](int v, float4 &a, float4 &gv) {
-                    int slot;
-                    a = sym_fetch_pos(st, v, w1, src, slot);
-                    gv = make_float4(gx[slot], gy[slot], gz[slot], 0.f);
-                    if (v >= w1) gv = make_float4(0.f, 0.f, 0.f, 0.f);
-                };
-                for (int p = p0; p < p1; ++p) {
-                    const int b = c0s + p * kWave + lane;
-                    const float px = src.x[b], py = src.y[b], pz = src.z[b], mk = src.m[b];
-                    const float gkx = gx[b], gky = gy[b], gkz = gz[b];
-                    const Box box = target_box(true, px, py, pz, false, 0.f, 0.f, 0.f);
-                    float rx = 0.f, ry = 0.f, rz = 0.f;
-                    if (p * kWave >= w0 && p * kWave < w1) {
-                        __syncthreads();
-                        tile_p[lane] = make_float4(px, py, pz, mk);
-                        tile_p[lane + kWave] = tile_p[lane];
-                        tile_g[lane] = make_float4(gkx, gky, gkz, 0.f);
-                        tile_g[lane + kWave] = tile_g[lane];
-                        __syncthreads();
-                        float bx = 0.f, by = 0.f, bz = 0.f;
-                        for (int s = 1; s <= kWave / 2; ++s) {
-                            float4 sj = tile_p[lane + s];
-                            float4 sg = tile_g[lane + s];
-                            if (s == kWave / 2 && lane >= kWave / 2) {
-                                sj = make_float4(kFar, kFar, kFar, 0.f);
-                                sg = make_float4(0.f, 0.f, 0.f, 0.f);
-                            }
-                            sym_vjp_step<kSoft, kUM>(sj, sg, px, py, pz, mk, gkx, gky, gkz, eps2, tc2, cq, cd, rx,
-                                                     ry, rz, bx, by, bz);
-                            bx = rotate_down(bx);
-                            by = rotate_down(by);
-                            bz = rotate_down(bz);
+        for (int i = 0; i < 5; ++i) cd[i] = S.pc.dqa[i];
+        cd[4] = keep_in_vgpr(cd[4]);
+        SymStencil st;
+        sym_stencil_setup(S, c, start, nact, sym_base, sym_pref, lane, st);
+        const int D = __shfl(st.cnt, 0);
+        const int c0s = start[c];
+        const int tbase = sym_base[c] + kk * D;  // group 0: the target slots
+        const int p0 = g * K, p1 = min(p0 + K, D / kWave);
+        const int k_end = min((kk + 1) * R, (st.total + kW - 1) / kW);
+        // the group's windows in turn: the first stores each block's target sums
+        // to its slot, the next ones add to it (this wave alone writes the slot)
+        for (int k = kk * R; k < k_end; ++k) {
+            const bool first = k == kk * R;
+            const int w0 = k * kW, w1 = min(w0 + kW, st.total);
+            for (int i = lane; i < kW; i += kWave) red.x[i] = red.y[i] = red.z[i] = 0.f;
+            auto fetch_pg = [&](int v, float4 &a, float4 &gv) {
+                int slot;
+                a = sym_fetch_pos(st, v, w1, src, slot);
+                gv = make_float4(gx[slot], gy[slot], gz[slot], 0.f);
+                if (v >= w1) gv = make_float4(0.f, 0.f, 0.f, 0.f);
+            };
+            for (int p = p0; p < p1; ++p) {
+                const int b = c0s + p * kWave + lane;
+                const float px = src.x[b], py = src.y[b], pz = src.z[b], mk = src.m[b];
+                const float gkx = gx[b], gky = gy[b], gkz = gz[b];
+                const Box box = target_box(true, px, py, pz, false, 0.f, 0.f, 0.f);
+                float rx = 0.f, ry = 0.f, rz = 0.f;
+                if (p * kWave >= w0 && p * kWave < w1) {
+                    __syncthreads();
+                    tile_p[lane] = make_float4(px, py, pz, mk);
+                    tile_p[lane + kWave] = tile_p[lane];
+                    tile_g[lane] = make_float4(gkx, gky, gkz, 0.f);
+                    tile_g[lane + kWave] = tile_g[lane];
+                    __syncthreads();
+                    float bx = 0.f, by = 0.f, bz = 0.f;
+                    for (int s = 1; s <= kWave / 2; ++s) {
+                        float4 sj = tile_p[lane + s];
+                        float4 sg = tile_g[lane + s];
+                        if (s == kWave / 2 && lane >= kWave / 2) {
+                            sj = make_float4(kFar, kFar, kFar, 0.f);
+                            sg = make_float4(0.f, 0.f, 0.f, 0.f);
                         }
-                        const int r = p * kWave - w0 + ((lane + kWave / 2 + 1) & (kWave - 1));
-                        red.x[r] += bx;
-                        red.y[r] += by;
-                        red.z[r] += bz;
+                        sym_vjp_step<kSoft, kUM>(sj, sg, px, py, pz, mk, gkx, gky, gkz, eps2, tc2, cq, cd, rx,
+                                                 ry, rz, bx, by, bz);
+                        bx = rotate_down(bx);
+                        by = rotate_down(by);
+                        bz = rotate_down(bz);
                     }
-                    const int vs = max(w0, (p + 1) * kWave);
-                    sym_stream<2>(vs, w1, w0, box, cull2, lane, tile_p, tile_g, tix, fetch_pg,
-                                  [&](int my) {
+                    const int r = p * kWave - w0 + ((lane + kWave / 2 + 1) & (kWave - 1));
+                    red.x[r] += bx;
+                    red.y[r] += by;
+                    red.z[r] += bz;
+                }
+                const int vs = max(w0, (p + 1) * kWave);
+                sym_stream<2>(vs, w1, w0, box, cull2, lane, tile_p, tile_g, tix, fetch_pg,
+                              [&](int my) {
+                                  float bx = 0.f, by = 0.f, bz = 0.f;
+                                  const float4 *tp = tile_p + lane;
+                                  const float4 *tg = tile_g + lane;
+                                  for (int s = 0; s < kWave; s += 4) {
+#pragma unroll
+                                      for (int u = 0; u < 4; ++u) {
+                                          sym_vjp_step<kSoft, kUM>(tp[s + u], tg[s + u], px, py, pz, mk, gkx,
+                                                                   gky, gkz, eps2, tc2, cq, cd, rx, ry, rz,
+                                                                   bx, by, bz);
+                                          bx = rotate_down(bx);
+                                          by = rotate_down(by);
+                                          bz = rotate_down(bz);
+                                      }
+                                  }
+                                  if (my >= 0) {
+                                      red.x[my] += bx;
+                                      red.y[my] += by;
+                                      red.z[my] += bz;
+                                  }
+                              },
+                              [&](int chunks) {
+                                  const float4 *tp = tile_p + kWave + (lane & 15);
+                                  const float4 *tg = tile_g + kWave + (lane & 15);
+                                  for (int k = 0; k < chunks; ++k) {
+                                      row_chunk(tile_p, k, lane);
+                                      row_chunk(tile_g, k, lane);
                                       float bx = 0.f, by = 0.f, bz = 0.f;
-                                      const float4 *tp = tile_p + lane;
-                                      const float4 *tg = tile_g + lane;
-                                      for (int s = 0; s < kWave; s += 4) {
+                                      for (int s = 0; s < 16; s += 4) {
 #pragma unroll
                                           for (int u = 0; u < 4; ++u) {
-                                              sym_vjp_step<kSoft, kUM>(tp[s + u], tg[s + u], px, py, pz, mk, gkx,
-                                                                       gky, gkz, eps2, tc2, cq, cd, rx, ry, rz,
-                                                                       bx, by, bz);
-                                              bx = rotate_down(bx);
-                                              by = rotate_down(by);
-                                              bz = rotate_down(bz);
+                                              sym_vjp_step<kSoft, kUM>(tp[s + u], tg[s + u], px, py, pz, mk,
+                                                                       gkx, gky, gkz, eps2, tc2, cq, cd, rx,
+                                                                       ry, rz, bx, by, bz);
+                                              bx = rotate_row(bx);
+                                              by = rotate_row(by);
+                                              bz = rotate_row(bz);
                                           }
                                       }
-                                      if (my >= 0) {
+                                      bx = sum_rows(bx);
+                                      by = sum_rows(by);
+                                      bz = sum_rows(bz);
+                                      const int my = tix[16 * k + (lane & 15)];
+                                      if (lane < 16 && my >= 0) {
                                           red.x[my] += bx;
                                           red.y[my] += by;
                                           red.z[my] += bz;
                                       }
-                                  },
-                                  [&](int chunks) {
-                                      const float4 *tp = tile_p + kWave + (lane & 15);
-                                      const float4 *tg = tile_g + kWave + (lane & 15);
-                                      for (int k = 0; k < chunks; ++k) {
-                                          row_chunk(tile_p, k, lane);
-                                          row_chunk(tile_g, k, lane);
-                                          float bx = 0.f, by = 0.f, bz = 0.f;
-                                          for (int s = 0; s < 16; s += 4) {
-#pragma unroll
-                                              for (int u = 0; u < 4; ++u) {
-                                                  sym_vjp_step<kSoft, kUM>(tp[s + u], tg[s + u], px, py, pz, mk,
-                                                                           gkx, gky, gkz, eps2, tc2, cq, cd, rx,
-                                                                           ry, rz, bx, by, bz);
-                                                  bx = rotate_row(bx);
-                                                  by = rotate_row(by);
-                                                  bz = rotate_row(bz);
-                                              }
-                                          }
-                                          bx = sum_rows(bx);
-                                          by = sum_rows(by);
-                                          bz = sum_rows(bz);
-                                          const int my = tix[16 * k + (lane & 15)];
-                                          if (lane < 16 && my >= 0) {
-                                              red.x[my] += bx;
-                                              red.y[my] += by;
-                                              red.z[my] += bz;
-                                          }
-                                      }
-                                  });
-                    const int64_t o = 3 * ((int64_t)tbase + p * kWave + lane);
-                    if (first) {
-                        pool[o] = rx;
-                        pool[o + 1] = ry;
-                        pool[o + 2] = rz;
-                    } else {
-                        pool[o] += rx;
-                        pool[o + 1] += ry;
-                        pool[o + 2] += rz;
-                    }
+                                  }
+                              });
+                const int64_t o = 3 * ((int64_t)tbase + p * kWave + lane);
+                if (first) {
+                    pool[o] = rx;
+                    pool[o + 1] = ry;
+                    pool[o + 2] = rz;
+                } else {
+                    pool[o] += rx;
+                    pool[o + 1] += ry;
+                    pool[o + 2] += rz;
                 }
-                __syncthreads();
-                for (int i = 0; i < w1 - w0; i += kWave) {
-                    const int v = w0 + i + lane;
-                    const int q = sym_locate(st, v);
-                    const int64_t slot = (int64_t)__shfl(st.sbase, q) + (int64_t)g * __shfl(st.cnt, q) +
-                                         (min(v, st.total - 1) - __shfl(st.excl, q));
-                    if (v < w1) {
-                        pool[3 * slot] = red.x[i + lane];
-                        pool[3 * slot + 1] = red.y[i + lane];
-                        pool[3 * slot + 2] = red.z[i + lane];
-                    }
-                }
-                __syncthreads();
             }
+            __syncthreads();
+            for (int i = 0; i < w1 - w0; i += kWave) {
+                const int v = w0 + i + lane;
+                const int q = sym_locate(st, v);
+                const int64_t slot = (int64_t)__shfl(st.sbase, q) + (int64_t)g * __shfl(st.cnt, q) +
+                                     (min(v, st.total - 1) - __shfl(st.excl, q));
+                if (v < w1) {
+                    pool[3 * slot] = red.x[i + lane];
+                    pool[3 * slot + 1] = red.y[i + lane];
+                    pool[3 * slot + 2] = red.z[i + lane];
+                }
+            }
+            __syncthreads();
         }
     }
-    guard.report(hdr, lane);
+    queue.guard.report(hdr, lane);
 }
 
 template <class Acc, bool kSoft, int kW, int kOcc>
