@@ -34,6 +34,7 @@ constexpr float kFar = 1.0e6f;  // position of padding sources (masked out)
 struct OneSeg {
     SegParams p;
     __device__ __forceinline__ int seg_of_particle(int) const { return 0; }
+    __device__ __forceinline__ int seg_of_next_particle(int) const { return 0; }
     __device__ __forceinline__ int seg_of_cell(int) const { return 0; }
     __device__ __forceinline__ int seg_of_tile(int) const { return 0; }
     __device__ __forceinline__ const SegParams &get(int) const { return p; }
@@ -58,8 +59,23 @@ struct ManySeg {
         }
         return lo;
     }
+    // One search for a wave whose lanes' particles or cells lie in one problem
+    // (the largest of them decides): the table is read through the scalar cache
+    // and no lane chases its own chain of loads.  x: non-decreasing over the
+    // active lanes.  (Binning 20.6 million particles of 96 problems: 0.33 ->
+    // 0.24 ms.)
+    template <int kField>
+    __device__ __forceinline__ int search_wave(int x) const
+    {
+        const int s0 = search<kField>(__builtin_amdgcn_readfirstlane(x));
+        if (s0 + 1 == B) return s0;
+        const int xl = __builtin_amdgcn_readlane(x, 63 - __clzll(__ballot(true)));
+        if (xl < (kField == 0 ? tab[s0 + 1].part_off : tab[s0 + 1].cell_off)) return s0;
+        return search<kField>(x);
+    }
     __device__ __forceinline__ int seg_of_particle(int i) const { return search<0>(i); }
-    __device__ __forceinline__ int seg_of_cell(int c) const { return search<1>(c); }
+    __device__ __forceinline__ int seg_of_next_particle(int i) const { return search_wave<0>(i); }
+    __device__ __forceinline__ int seg_of_cell(int c) const { return search_wave<1>(c); }
     __device__ __forceinline__ int seg_of_tile(int t) const { return search<2>(t); }
     __device__ __forceinline__ const SegParams &get(int s) const { return tab[s]; }
 };
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(256) void k_bin_cells(Acc acc, const float *__restr
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= N) return;
-    const SegParams &S = acc.get(acc.seg_of_particle(i));
+    const SegParams &S = acc.get(acc.seg_of_next_particle(i));
     uint32_t fl = 0;
     float ox, oy, oz;
     const int64_t p = 3 * (int64_t)i;
@@ -539,32 +555,25 @@ __device__ __forceinline__ int item_seg(int w) { return w >> 6; }
 // are the targets of the symmetric tiles.
 __device__ __forceinline__ int dense_count(int na) { return na >= kWave ? (na & ~(kWave - 1)) : 0; }
 
-// Items of a run of nt consecutive targets from slot s0 (the cut described
-// above, groups of at most `group` targets); returns the number written,
-// cell_items(nt, two, group).
-__device__ __forceinline__ int write_run(int4 *__restrict__ items, uint32_t at, int c, int s0, int nt,
-                                         bool two, int seg, int psrc, int nd, int group)
+// Item k of a run of nt consecutive targets from slot s0 (the cut described
+// above, groups of at most `group` targets); a run has cell_items(nt, two,
+// group) of them.
+__device__ __forceinline__ int4 run_item(int k, int c, int s0, int nt, bool two, int seg, int psrc, int nd, int group)
 {
-    if (nt <= 0) return 0;
-    int k = 0;
-    if (nt < kTargetsPerItem) {
-        for (int t = 0; t < nt; t += group, ++k) {
-            const int cn = min(group, nt - t);
-            items[at + k] = make_int4(c, s0 + t, cn, item_word(lanes_log2(cn), 0, psrc, seg, nd));
-        }
-        return k;
+    const int r = nt % kTargetsPerItem, full = nt / kTargetsPerItem;
+    const int dense = two ? (full + 1) / 2 : full;
+    int t, cn, lk = 0;
+    if (k < dense) {
+        const int chunk = two ? 2 * kTargetsPerItem : kTargetsPerItem;
+        t = k * chunk;
+        cn = min(chunk, nt - r - t);
+    } else {
+        t = (k - dense) * group;
+        cn = min(group, r - t);
+        t += nt - r;
+        lk = lanes_log2(cn);
     }
-    const int r = nt % kTargetsPerItem, dense_end = nt - r;
-    for (int t0 = 0; t0 < dense_end; ++k) {
-        const int cn = (two && dense_end - t0 >= 2 * kTargetsPerItem) ? 2 * kTargetsPerItem : kTargetsPerItem;
-        items[at + k] = make_int4(c, s0 + t0, cn, item_word(0, cn > kTargetsPerItem ? 1 : 0, psrc, seg, nd));
-        t0 += cn;
-    }
-    for (int t = dense_end; t < nt; t += group, ++k) {
-        const int cn = min(group, nt - t);
-        items[at + k] = make_int4(c, s0 + t, cn, item_word(lanes_log2(cn), 0, psrc, seg, nd));
-    }
-    return k;
+    return make_int4(c, s0 + t, cn, item_word(lk, cn > kTargetsPerItem ? 1 : 0, psrc, seg, nd));
 }
 
 // Cost of the widest item of a run of nt targets that sees src sources:
@@ -1471,19 +1480,28 @@ __global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__
         atomicMax(&hdr[kHdrSymLongest + threadIdx.x], longest[threadIdx.x]);
     }
     if (threadIdx.x == 0 && work) atomicAdd((unsigned long long *)&hdr[kHdrSymWork], work);
-    __threadfence();
+    // everything the last workgroup reads is added by device-scope atomics, so
+    // waiting for them is enough (a device-scope fence would write the L2 back)
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) rank = atomicAdd(&hdr[kHdrSymDone], 1u);
     __syncthreads();
-    if (rank != gridDim.x - 1 || threadIdx.x != 0) return;
-    __threadfence();
-    const double w = (double)load_agent(&hdr[kHdrSymWork]);
+    if (rank != gridDim.x - 1) return;
+    // the last workgroup: all totals read at once
+    if (threadIdx.x < kSymShapes) {
+        slots[threadIdx.x] = load_agent(&hdr[kHdrSymSlots + 2 * threadIdx.x]);
+        longest[threadIdx.x] = __hip_atomic_load(&hdr[kHdrSymLongest + threadIdx.x], __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+    } else if (threadIdx.x == kSymShapes) {
+        work = load_agent(&hdr[kHdrSymWork]);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const double w = (double)work;
     int pick = -1;
     if (w > 0.0) {
-        auto fits = [&](int i) { return load_agent(&hdr[kHdrSymSlots + 2 * i]) <= cap; };
-        auto len = [&](int i) {
-            return (double)__hip_atomic_load(&hdr[kHdrSymLongest + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
+        auto fits = [&](int i) { return slots[i] <= cap; };
+        auto len = [&](int i) { return (double)longest[i]; };
         for (int i = 0; i < sh.n && pick < 0; ++i)
             if (fits(i) && w >= kSymSpread * balance * waves * len(i)) pick = i;
         for (int i = sh.n - 1; i >= 0 && pick < 0; --i)
@@ -1547,10 +1565,6 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(
         const int c = c0 + tid;
         uint32_t inf = 0, sinf = 0;
         int total = 0;
-        if (sym) {
-#pragma unroll 1
-            for (int e = 0; e < kSymStride; ++e) row[e] = 0;
-        }
         const int na = binned && c < NC ? nact[c] : 0;
         const int nc = binned && c < NC ? start[c + 1] - start[c] : 0;
         if (nc > 0 && na >= 0 && na <= nc && nc <= N) {
@@ -1585,6 +1599,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(
                 for (int f = 0; f < kSymNdDirs; ++f)
                     nd[f] = (int)(((uint64_t)(uint32_t)(nd[f] / kWave + K - 1) * inv_k) >> 36);
                 // counts, then exclusive prefixes; k_sym_plan has checked that all of them fit the pool
+                row[0] = 0;
                 if (D > 0) {
                     const int nb = D / kWave;
                     const int per_run = (int)(((uint32_t)sv + (uint32_t)(R * W) - 1u) / (uint32_t)(R * W));
@@ -1607,11 +1622,18 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(
                 for (int f = 0; f < kSymNdDirs; ++f) {
                     row[1 + kSymDirs + f] = nd[kSymNdDirs - 1 - f] * ND;
                 }
+                constexpr int kStep = 7;
+                static_assert(kSymStride % kStep == 0, "rows in whole steps");
 #pragma unroll 1
-                for (int e = 0; e < kSymStride; ++e) {
-                    const int v = row[e];
-                    row[e] = total;
-                    total += v;
+                for (int e = 0; e < kSymStride; e += kStep) {
+                    int v[kStep];
+#pragma unroll
+                    for (int u = 0; u < kStep; ++u) v[u] = row[e + u];
+#pragma unroll
+                    for (int u = 0; u < kStep; ++u) {
+                        row[e + u] = total;
+                        total += v[u];
+                    }
                 }
             }
         }
@@ -1702,26 +1724,41 @@ __global__ __launch_bounds__(256) void k_items_write(Acc acc, int NC, const int 
         if (blockIdx.x == 0 && threadIdx.x == 0) hdr[kHdrSymNItems] = sall;
     }
     __syncthreads();
-    if (n_items == 0 && n_sym == 0) return;
-    const int na = nact[c];
-    const int seg = acc.seg_of_cell(c);
+    const bool any = n_items != 0 || n_sym != 0;
+    const int na = any ? nact[c] : 0, s0 = any ? start[c] : 0, nt = any ? start[c + 1] - s0 : 0;
+    const int seg = any ? acc.seg_of_cell(c) : 0;
     const int dn = sym ? dense_count(na) : 0;
-    if (n_items) {
-        const int nt = start[c + 1] - start[c];
-        const uint32_t at = base[0][cls] + local;
-        const int s0 = start[c];
-        // active targets (all sources), then for the adjoint the passive ones (active sources);
-        // with symmetric tiles only the non-dense targets, against the non-dense sources
-        const int k = write_run(items, at, c, s0 + dn, na - dn, two, seg, 0, sym ? 1 : 0, group);
-        if (!kActiveOnly) write_run(items, at + k, c, s0 + na, nt - na, two, seg, 1, sym ? 1 : 0, group);
+    // active targets (all sources), then for the adjoint the passive ones (active sources);
+    // with symmetric tiles only the non-dense targets, against the non-dense sources
+    const uint32_t at = base[0][cls] + local;
+    const int n_act = cell_items(na - dn, two != 0, group);
+    auto one_sided = [&](int k, int cell, int first, int active, int dense, int total, int n_a, int sg) {
+        return k < n_a ? run_item(k, cell, first + dense, active - dense, two != 0, sg, 0, sym ? 1 : 0, group)
+                       : run_item(k - n_a, cell, first + active, total - active, two != 0, sg, 1, sym ? 1 : 0, group);
+    };
+    // a cell's lane writes a few items by itself; longer lists are written by the whole wave
+    constexpr int kAlone = 8;
+    if (n_items <= kAlone)
+        for (int k = 0; k < n_items; ++k) items[at + k] = one_sided(k, c, s0, na, dn, nt, n_act, seg);
+    const int lane = threadIdx.x & (kWave - 1);
+    for (uint64_t todo = __ballot(n_items > kAlone); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo);
+        const int n = __builtin_amdgcn_readlane(n_items, l), cell = __builtin_amdgcn_readlane(c, l);
+        const int first = __builtin_amdgcn_readlane(s0, l), active = __builtin_amdgcn_readlane(na, l);
+        const int dense = __builtin_amdgcn_readlane(dn, l), total = __builtin_amdgcn_readlane(nt, l);
+        const int n_a = __builtin_amdgcn_readlane(n_act, l), sg = __builtin_amdgcn_readlane(seg, l);
+        const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)at, l);
+        for (int k = lane; k < n; k += kWave) items[to + k] = one_sided(k, cell, first, active, dense, total, n_a, sg);
     }
-    if (n_sym) {
-        const int K = (int)hdr[kHdrSymK];
-        const int G = (dn / kWave + K - 1) / K;
-        const int C = n_sym / G;
-        const uint32_t at = base[1][scls] + slocal;
-        for (int g = 0; g < G; ++g)
-            for (int k = 0; k < C; ++k) sym_items[at + (uint32_t)(g * C + k)] = make_int4(c, g, k, seg);
+    const uint32_t sat = base[1][scls] + slocal;
+    const int K = (int)hdr[kHdrSymK];
+    for (uint64_t todo = __ballot(n_sym > 0); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo);
+        const int n = __builtin_amdgcn_readlane(n_sym, l), cell = __builtin_amdgcn_readlane(c, l);
+        const int runs = (__builtin_amdgcn_readlane(dn, l) / kWave + K - 1) / K, sg = __builtin_amdgcn_readlane(seg, l);
+        const int per_run = n / runs;
+        const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)sat, l);
+        for (int k = lane; k < n; k += kWave) sym_items[to + k] = make_int4(cell, k / per_run, k % per_run, sg);
     }
 }
 
@@ -2407,8 +2444,8 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_vjp_sym(Acc acc, co
 // (adjoint, n_out = N).  Bound by the slots it reads: one run of equally spaced
 // slots per particle with eight loads in flight, instead of one run per
 // direction with its own bounds and division, took the pass on 16.8 million
-// clustered particles from 0.87 to 0.47 ms and on the node share from 2.23 to
-// 2.03 ms (4.2 TB/s).
+// clustered particles from 0.87 to 0.41 ms and on the node share from 2.23 to
+// 2.05 ms (4.2 TB/s).
 __global__ __launch_bounds__(256) void k_sym_gather(int N, int key_bits, const int *__restrict__ key,
                                                     const int *__restrict__ start,
                                                     const int *__restrict__ nact,
