@@ -170,7 +170,8 @@ struct RadixBufs {
     int *scan_tmp;  // scan_scratch_elems(table) entries
 };
 hipError_t radix_sort_pairs(const int *keys_in, const int *vals_in, int64_t n, int passes,
-                            int digit_bits, int64_t ntiles, const RadixBufs &b, hipStream_t st);
+                            int digit_bits, int64_t ntiles, const RadixBufs &b, hipStream_t st,
+                            bool counted = false);
 hipError_t dev_scan(const int *in, int *out, int64_t m, int *tmp, hipStream_t st);
 hipError_t dev_bounds(const int *sorted_keys, int64_t n, int64_t nk, int key_bits, int *start,
                       hipStream_t st);

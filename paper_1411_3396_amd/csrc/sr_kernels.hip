@@ -169,6 +169,14 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
     if (i < n) p[i] = v;
 }
 
+// Zeroes two arrays.
+__global__ void k_clear(uint32_t *p, int64_t n, uint32_t *q, int64_t m)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0u;
+    else if (i < n + m) q[i - n] = 0u;
+}
+
 hipError_t fill_u32(void *p, int64_t n, uint32_t v, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
@@ -293,33 +301,58 @@ __device__ __forceinline__ int leaf_code(float ox, float oy, float oz, const Seg
 // Cell of each particle and its sort key: (cell, passive, leaf code).  With
 // key_bits == code_bits there is no passive bit (every particle is active).
 // The offsets from the cell centre and the mass are kept in input order, one
-// float4 per particle, for the gather into binned order.
+// float4 per particle, for the gather into binned order.  A workgroup takes
+// one radix tile and counts the first pass's digits on the way (`digit_at`
+// says where they go), which saves that pass its histogram.
+constexpr int kBinThreads = 512;
+
+// Entry of digit d of tile t in a digit table: tile by tile for the sorts
+// whose scatter adds up the tables itself, else digit by digit for a scan.
+__device__ __forceinline__ int64_t digit_at(int d, int t, int R, int ntiles, bool by_tile)
+{
+    return by_tile ? (int64_t)t * R + d : (int64_t)d * ntiles + t;
+}
+
 template <class Acc>
-__global__ __launch_bounds__(256) void k_bin_cells(Acc acc, const float *__restrict__ pos,
+__global__ __launch_bounds__(kBinThreads) void k_bin_cells(Acc acc, const float *__restrict__ pos,
                                                    const float *__restrict__ mass, int N,
                                                    int key_bits, int code_bits, int *__restrict__ cell_of,
                                                    int *__restrict__ skey, float4 *__restrict__ packed,
-                                                   uint32_t *hdr)
+                                                   uint32_t *hdr, int bits, int *__restrict__ table, int ntiles,
+                                                   int by_tile)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= N) return;
-    const SegParams &S = acc.get(acc.seg_of_next_particle(i));
+    __shared__ int h[256];
+    const int R = 1 << bits;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    __syncthreads();
     uint32_t fl = 0;
-    float ox, oy, oz;
-    const int64_t p = 3 * (int64_t)i;
-    const int ix = bin_coord(pos[p], S.lo[0], S.len[0], S.inv_len[0], S.h[0], S.inv_h[0], S.nc[0],
-                             S.periodic, ox, fl);
-    const int iy = bin_coord(pos[p + 1], S.lo[1], S.len[1], S.inv_len[1], S.h[1], S.inv_h[1],
-                             S.nc[1], S.periodic, oy, fl);
-    const int iz = bin_coord(pos[p + 2], S.lo[2], S.len[2], S.inv_len[2], S.h[2], S.inv_h[2],
-                             S.nc[2], S.periodic, oz, fl);
-    const int cell = S.cell_off + (ix * S.nc[1] + iy) * S.nc[2] + iz;
-    const int code = leaf_code(ox, oy, oz, S);
-    const int passive = (i - S.part_off < S.n_active) ? 0 : 1;
-    cell_of[i] = cell;
-    skey[i] = (cell << key_bits) | (key_bits > code_bits ? passive << code_bits : 0) | code;
-    packed[i] = make_float4(ox, oy, oz, mass[i]);
+#pragma unroll
+    for (int r = 0; r < kRadixTile / kBinThreads; ++r) {
+        const int64_t e = (int64_t)blockIdx.x * kRadixTile + r * kBinThreads + threadIdx.x;
+        if (e >= N) break;
+        const int i = (int)e;
+        const SegParams &S = acc.get(acc.seg_of_next_particle(i));
+        float ox, oy, oz;
+        const int64_t p = 3 * (int64_t)i;
+        const int ix = bin_coord(pos[p], S.lo[0], S.len[0], S.inv_len[0], S.h[0], S.inv_h[0], S.nc[0],
+                                 S.periodic, ox, fl);
+        const int iy = bin_coord(pos[p + 1], S.lo[1], S.len[1], S.inv_len[1], S.h[1], S.inv_h[1],
+                                 S.nc[1], S.periodic, oy, fl);
+        const int iz = bin_coord(pos[p + 2], S.lo[2], S.len[2], S.inv_len[2], S.h[2], S.inv_h[2],
+                                 S.nc[2], S.periodic, oz, fl);
+        const int cell = S.cell_off + (ix * S.nc[1] + iy) * S.nc[2] + iz;
+        const int code = leaf_code(ox, oy, oz, S);
+        const int passive = (i - S.part_off < S.n_active) ? 0 : 1;
+        const int key = (cell << key_bits) | (key_bits > code_bits ? passive << code_bits : 0) | code;
+        cell_of[i] = cell;
+        skey[i] = key;
+        packed[i] = make_float4(ox, oy, oz, mass[i]);
+        atomicAdd(&h[key & (R - 1)], 1);
+    }
     if (fl) atomicOr(&hdr[kHdrFlags], fl);
+    __syncthreads();
+    const int d = threadIdx.x;
+    if (d < R) table[digit_at(d, blockIdx.x, R, ntiles, by_tile != 0)] = h[d];
 }
 
 // Cell starts from the sorted cell keys: slot b starts every cell in
@@ -336,9 +369,9 @@ __global__ __launch_bounds__(256) void k_cell_bounds(const int *__restrict__ key
 
 // --------------------------------------------------------------- A2: stable radix sort
 
-// Digit histogram of one tile: table[d * ntiles + tile].
+// Digit histogram of one tile.
 __global__ __launch_bounds__(256) void k_radix_hist(const int *__restrict__ keys, int N, int shift,
-                                                    int bits, int *__restrict__ table, int ntiles)
+                                                    int bits, int *__restrict__ table, int ntiles, int by_tile)
 {
     __shared__ int h[256];
     const int R = 1 << bits;
@@ -350,46 +383,74 @@ __global__ __launch_bounds__(256) void k_radix_hist(const int *__restrict__ keys
         if (k < N) atomicAdd(&h[(keys[k] >> shift) & (R - 1)], 1);
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < R; d += 256) table[(int64_t)d * ntiles + blockIdx.x] = h[d];
+    for (int d = threadIdx.x; d < R; d += 256) table[digit_at(d, blockIdx.x, R, ntiles, by_tile != 0)] = h[d];
 }
 
-// Stable scatter of one tile of kRadixTile elements by four waves.  Each
-// wave ranks its quarter of the tile (consecutive elements, 64 at a time)
+// Stable scatter of one tile of kRadixTile elements by kWaves waves.  Each
+// wave ranks its part of the tile (consecutive elements, 64 at a time)
 // with one ballot per digit bit and per-wave digit counters.  The tile is then
 // reordered by digit in LDS, keeping input order inside a digit (wave, then
 // step, then lane), and written out in that order: each digit's run of the
-// tile lands on consecutive global addresses.
+// tile lands on consecutive global addresses.  table: with kDirect the digit
+// counts of every tile (tile by tile), which the workgroup adds up itself to
+// find where its digits start; otherwise their exclusive scan.
+//
+// kDirect serves sorts of at most kDirectTiles tiles: the scan's three
+// launches, some 4.5 us each, are most of such a sort, and 128 tiles are 128
+// loads per digit, all in flight.  It takes 16 waves a tile, since there are
+// fewer tiles than CUs and the ranking is a chain of kRadixTile / 64 / kWaves
+// steps.
+constexpr int kDirectTiles = 128;
+constexpr int kDirectWaves = 16;
 constexpr int kScatterWaves = 4;
-constexpr int kScatterSteps = kRadixTile / (kScatterWaves * kWave);
 
-__global__ __launch_bounds__(kScatterWaves * kWave) void k_radix_scatter(
+template <int kWaves, bool kDirect>
+__global__ __launch_bounds__(kWaves * kWave) void k_radix_scatter(
     const int *__restrict__ keys_in, const int *__restrict__ vals_in, int N, int shift, int bits,
-    const int *__restrict__ table_x, int ntiles, int *__restrict__ keys_out, int *__restrict__ vals_out)
+    const int *__restrict__ table, int ntiles, int *__restrict__ keys_out, int *__restrict__ vals_out)
 {
-    constexpr int kThreads = kScatterWaves * kWave;
-    __shared__ int cnt[kScatterWaves][256];  // per-wave digit counts, then per-wave offsets
-    __shared__ int lstart[256];              // first slot of each digit in the reordered tile
-    __shared__ int gstart[256];              // first global slot of each digit of this tile
-    __shared__ int wsum[kScatterWaves];
+    constexpr int kThreads = kWaves * kWave;
+    constexpr int kSteps = kRadixTile / kThreads;
+    static_assert(kThreads >= 256, "one thread per digit");
+    __shared__ int cnt[kWaves][256];  // per-wave digit counts, then per-wave offsets
+    __shared__ int lstart[256];       // first slot of each digit in the reordered tile
+    __shared__ int gstart[256];       // first global slot of each digit of this tile
+    __shared__ int wsum[4], gsum[4];
     __shared__ int lkey[kRadixTile];
     __shared__ int lval[kRadixTile];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int R = 1 << bits;
     const int tile = blockIdx.x;
-    gstart[tid] = tid < R ? table_x[(int64_t)tid * ntiles + tile] : 0;
-#pragma unroll
-    for (int w = 0; w < kScatterWaves; ++w) cnt[w][tid] = 0;
+    // a digit's place: its elements of earlier tiles and (kDirect, added below) all of smaller digits
+    int g_before = 0, g_total = 0;
+    if (tid < R) {
+        if constexpr (kDirect) {
+#pragma unroll 8
+            for (int t = 0; t < ntiles; ++t) {
+                const int v = table[(int64_t)t * R + tid];
+                g_total += v;
+                g_before += t < tile ? v : 0;
+            }
+        } else {
+            g_before = table[(int64_t)tid * ntiles + tile];
+        }
+    }
+    for (int i = tid; i < kWaves * 256; i += kThreads) (&cnt[0][0])[i] = 0;
     __syncthreads();
     const int64_t tile0 = (int64_t)tile * kRadixTile;
-    const int64_t base = tile0 + (int64_t)wv * (kScatterSteps * kWave);
+    const int64_t base = tile0 + (int64_t)wv * (kSteps * kWave);
     const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    int key[kScatterSteps], val[kScatterSteps], rk[kScatterSteps];
+    int key[kSteps], val[kSteps], rk[kSteps];
 #pragma unroll
-    for (int r = 0; r < kScatterSteps; ++r) {
+    for (int r = 0; r < kSteps; ++r) {
         const int64_t e = base + r * kWave + lane;
         const bool valid = e < N;
         key[r] = valid ? keys_in[e] : 0;
         val[r] = valid ? (vals_in ? vals_in[e] : (int)e) : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kSteps; ++r) {
+        const bool valid = base + r * kWave + lane < N;
         const int d = (key[r] >> shift) & (R - 1);
         uint64_t peers = __ballot(valid);
         for (int b = 0; b < bits; ++b) {
@@ -404,30 +465,45 @@ __global__ __launch_bounds__(kScatterWaves * kWave) void k_radix_scatter(
         if (valid && rank == 0) cnt[wv][d] = before + __popcll(peers);
         __syncthreads();
     }
-    // per-wave offsets inside each digit, and the digit totals
-    int tot = 0;
+    // per-wave offsets inside each digit, and exclusive scans over the 256 digits (one per
+    // thread of the first four waves) of the tile's totals and (kDirect) of all tiles'
+    int tot = 0, incl = 0, g_incl = g_total;
+    if (tid < 256) {
 #pragma unroll
-    for (int w = 0; w < kScatterWaves; ++w) {
-        const int c = cnt[w][tid];
-        cnt[w][tid] = tot;
-        tot += c;
+        for (int w = 0; w < kWaves; ++w) {
+            const int c = cnt[w][tid];
+            cnt[w][tid] = tot;
+            tot += c;
+        }
+        incl = tot;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(incl, o);
+            const int z = kDirect ? __shfl_up(g_incl, o) : 0;
+            if (lane >= o) {
+                incl += y;
+                g_incl += z;
+            }
+        }
+        if (lane == kWave - 1) {
+            wsum[wv] = incl;
+            gsum[wv] = g_incl;
+        }
     }
-    // exclusive scan of the totals over the 256 digits (one per thread)
-    int incl = tot;
+    __syncthreads();
+    if (tid < 256) {
+        int prior = 0, g_prior = 0;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
+        for (int w = 0; w < 4; ++w) {
+            prior += w < wv ? wsum[w] : 0;
+            g_prior += w < wv ? gsum[w] : 0;
+        }
+        lstart[tid] = prior + incl - tot;
+        gstart[tid] = g_before + (kDirect ? g_prior + g_incl - g_total : 0);
     }
-    if (lane == kWave - 1) wsum[wv] = incl;
-    __syncthreads();
-    int prior = 0;
-#pragma unroll
-    for (int w = 0; w < kScatterWaves; ++w) prior += w < wv ? wsum[w] : 0;
-    lstart[tid] = prior + incl - tot;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kScatterSteps; ++r) {
+    for (int r = 0; r < kSteps; ++r) {
         if (rk[r] >= 0) {
             const int d = (key[r] >> shift) & (R - 1);
             const int at = lstart[d] + cnt[wv][d] + rk[r];
@@ -2716,29 +2792,39 @@ hipError_t dev_bounds(const int *sorted_keys, int64_t n, int64_t nk, int key_bit
     return hipGetLastError();
 }
 
+bool radix_direct(int64_t ntiles) { return ntiles <= kDirectTiles; }
+
 // Stable LSD radix sort of (key, value) pairs: keys in [0, 2^(passes*digit_bits)),
 // values default to the element index.  The result is in keys[(passes-1)&1],
-// vals[(passes-1)&1].
+// vals[(passes-1)&1].  counted: the first pass's digit counts are in b.tab
+// (laid out as radix_direct says).
 hipError_t radix_sort_pairs(const int *keys_in, const int *vals_in, int64_t n, int passes,
-                            int digit_bits, int64_t ntiles, const RadixBufs &b, hipStream_t st)
+                            int digit_bits, int64_t ntiles, const RadixBufs &b, hipStream_t st, bool counted)
 {
     if (n <= 0) return hipSuccess;
     if (digit_bits < 1 || digit_bits > 8 || passes < 1) return hipErrorInvalidValue;
     const int *kin = keys_in;
     const int *vin = vals_in;
     const int R = 1 << digit_bits;
+    const bool direct = radix_direct(ntiles);
     hipError_t e;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * digit_bits;
         int *kout = b.keys[p & 1];
         int *vout = b.vals[p & 1];
-        k_radix_hist<<<(unsigned)ntiles, 256, 0, st>>>(kin, (int)n, shift, digit_bits, b.tab,
-                                                     (int)ntiles);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = scan_i32(b.tab, b.tabx, (int64_t)R * ntiles, b.scan_tmp, st)) != hipSuccess) return e;
-        k_radix_scatter<<<(unsigned)ntiles, kScatterWaves * kWave, 0, st>>>(kin, vin, (int)n, shift,
-                                                                           digit_bits, b.tabx,
-                                                        (int)ntiles, kout, vout);
+        if (p > 0 || !counted) {
+            k_radix_hist<<<(unsigned)ntiles, 256, 0, st>>>(kin, (int)n, shift, digit_bits, b.tab, (int)ntiles,
+                                                           direct ? 1 : 0);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        if (direct) {
+            k_radix_scatter<kDirectWaves, true><<<(unsigned)ntiles, kDirectWaves * kWave, 0, st>>>(
+                kin, vin, (int)n, shift, digit_bits, b.tab, (int)ntiles, kout, vout);
+        } else {
+            if ((e = scan_i32(b.tab, b.tabx, (int64_t)R * ntiles, b.scan_tmp, st)) != hipSuccess) return e;
+            k_radix_scatter<kScatterWaves, false><<<(unsigned)ntiles, kScatterWaves * kWave, 0, st>>>(
+                kin, vin, (int)n, shift, digit_bits, b.tabx, (int)ntiles, kout, vout);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         kin = kout;
         vin = vout;
@@ -2749,23 +2835,23 @@ hipError_t radix_sort_pairs(const int *keys_in, const int *vals_in, int64_t n, i
 hipError_t dev_bin(const DevArgs &a, const float *pos, const float *mass)
 {
     const Layout &L = *a.L;
-    hipError_t e;
-    if ((e = fill_u32(at<uint32_t>(a, L.hdr), kHdrWords, 0, a.st)) != hipSuccess) return e;
-    if ((e = fill_u32(at<uint32_t>(a, L.nact), L.NC, 0, a.st)) != hipSuccess) return e;
-    if (L.N == 0) return hipSuccess;
+    k_clear<<<blocks_for(kHdrWords + L.NC, 256), 256, 0, a.st>>>(at<uint32_t>(a, L.hdr), kHdrWords,
+                                                                at<uint32_t>(a, L.nact), L.NC);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || L.N == 0) return e;
     e = with_acc(a, [&](auto acc) -> hipError_t {
-        k_bin_cells<<<blocks_for(L.N, 256), 256, 0, a.st>>>(acc, pos, mass, (int)L.N, L.key_bits, L.code_bits,
-                                                             at<int>(a, L.cell_of), at<int>(a, L.skey),
-                                                             at<float4>(a, L.packed),
-                                                             at<uint32_t>(a, L.hdr));
+        k_bin_cells<<<(unsigned)L.ntiles, kBinThreads, 0, a.st>>>(
+            acc, pos, mass, (int)L.N, L.key_bits, L.code_bits, at<int>(a, L.cell_of), at<int>(a, L.skey),
+            at<float4>(a, L.packed), at<uint32_t>(a, L.hdr), L.digit_bits, at<int>(a, L.tab), (int)L.ntiles,
+            radix_direct(L.ntiles) ? 1 : 0);
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
     RadixBufs rb{{at<int>(a, L.keys[0]), at<int>(a, L.keys[1])},
                  {at<int>(a, L.vals[0]), at<int>(a, L.vals[1])},
                  at<int>(a, L.tab), at<int>(a, L.tabx), at<int>(a, L.scan_tmp)};
-    if ((e = radix_sort_pairs(at<int>(a, L.skey), nullptr, L.N, L.passes, L.digit_bits, L.ntiles, rb,
-                              a.st)) != hipSuccess)
+    if ((e = radix_sort_pairs(at<int>(a, L.skey), nullptr, L.N, L.passes, L.digit_bits, L.ntiles, rb, a.st,
+                              true)) != hipSuccess)
         return e;
     if ((e = dev_bounds(at<int>(a, L.sorted_keys()), L.N, L.NC, L.key_bits, at<int>(a, L.start),
                         a.st)) != hipSuccess)

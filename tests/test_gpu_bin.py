@@ -115,3 +115,11 @@ def test_reuse_bins_on_unbinned_workspace_computes_nothing():
     sr.force(pos, mass, w.problem, w.n, ws=ws, reuse_bins=True, out=out)
     assert sr.ws_flags(ws) & 4
     assert torch.all(out == 7.0)
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 128 * 2048 - 1, 128 * 2048, 128 * 2048 + 1])
+def test_bin_order_at_the_edges_of_the_sorts(n):
+    # one tile and two, and the largest sort whose scatter adds up the tiles' digit
+    # counts itself and the smallest that scans them; clustered, so digits repeat
+    w = synth.clustered_box(n, 48.0, 12, n, halo_frac=0.5, mass_range=(1e2, 1e4))
+    check_bins(w)
