@@ -549,8 +549,8 @@ __global__ __launch_bounds__(256) void k_gather(Acc acc, int N, const int *__res
     bz[b] = v.z;
     const float mi = v.w;
     bm[b] = mi;
-    // not every mass equal (the plain read spares most of the adds to one address)
-    if (!(mi == packed[0].w) && hdr[kHdrMassInfo] == 0) atomicOr(&hdr[kHdrMassInfo], 1u);
+    // not every mass equal: the same word from every such wave, so a plain store
+    if (!(mi == packed[0].w)) hdr[kHdrMassInfo] = 1u;
     const int li = i - S.part_off;
     const bool act = li < S.n_active;
     out_row[b] = act ? S.out_off + li : -1;
@@ -1532,26 +1532,38 @@ __global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__
             // tile steps: every block meets every source
             const uint64_t steps = wave_sum((uint64_t)nb * (uint64_t)sv);
             if (first) atomicAdd(&work, (unsigned long long)steps);
-            for (int i = 0; i < sh.n; ++i) {
+            uint64_t need[kSymShapes];
+            uint32_t cost[kSymShapes];
+#pragma unroll
+            for (int i = 0; i < kSymShapes; ++i) {  // shapes past n repeat the last
                 const uint32_t rw = (uint32_t)(sh.R[i] * sh.W), k = (uint32_t)sh.K[i];
                 const uint64_t items = ((uint32_t)sv + rw - 1) / rw;  // per run; sv < 2^31
                 const uint64_t runs = ((uint32_t)nb + k - 1) / k;
-                uint64_t need = items * (uint64_t)D + runs * (uint64_t)sv;
-                if (items * runs >= (uint64_t(1) << 27)) need = uint64_t(1) << 42;  // beyond any pool
-                uint32_t cost = (uint32_t)min((uint64_t)min((uint32_t)nb, k) * min((uint64_t)rw, (uint64_t)sv),
-                                              (uint64_t)UINT32_MAX);
-                need = wave_sum(need);
+                need[i] = items * (uint64_t)D + runs * (uint64_t)sv;
+                if (items * runs >= (uint64_t(1) << 27)) need[i] = uint64_t(1) << 42;  // beyond any pool
+                cost[i] = (uint32_t)min((uint64_t)min((uint32_t)nb, k) * min((uint64_t)rw, (uint64_t)sv),
+                                        (uint64_t)UINT32_MAX);
+            }
+            // all shapes' sums over the wave side by side
 #pragma unroll
-                for (int o = kWave / 2; o >= 1; o >>= 1) cost = max(cost, (uint32_t)__shfl_xor((int)cost, o));
-                if (first) {
-                    atomicAdd(&slots[i], (unsigned long long)need);
-                    atomicMax(&longest[i], cost);
+            for (int o = kWave / 2; o >= 1; o >>= 1) {
+#pragma unroll
+                for (int i = 0; i < kSymShapes; ++i) {
+                    need[i] += (uint64_t)__shfl_xor((unsigned long long)need[i], o);
+                    cost[i] = max(cost[i], (uint32_t)__shfl_xor((int)cost[i], o));
+                }
+            }
+            if (first) {
+#pragma unroll
+                for (int i = 0; i < kSymShapes; ++i) {
+                    atomicAdd(&slots[i], (unsigned long long)need[i]);
+                    atomicMax(&longest[i], cost[i]);
                 }
             }
         }
     }
     __syncthreads();
-    if (threadIdx.x < sh.n && slots[threadIdx.x]) {
+    if (threadIdx.x < kSymShapes && slots[threadIdx.x]) {
         atomicAdd((unsigned long long *)&hdr[kHdrSymSlots + 2 * threadIdx.x], slots[threadIdx.x]);
         atomicMax(&hdr[kHdrSymLongest + threadIdx.x], longest[threadIdx.x]);
     }
@@ -2739,6 +2751,10 @@ hipError_t build_lists(const DevArgs &a, int two, bool sym)
                 add(a.sym_blocks / 4, 1);
                 add(a.sym_blocks / 8, 1);
                 add(a.sym_blocks / 16, 1);
+            }
+            for (int i = sh.n; i < kSymShapes; ++i) {
+                sh.K[i] = sh.K[sh.n - 1];
+                sh.R[i] = sh.R[sh.n - 1];
             }
             k_sym_plan<<<std::min(blocks_for(L.NC, 256), kListBlocks), 256, 0, a.st>>>(
                 acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), sh, hdr, L.magic(),
