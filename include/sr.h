@@ -363,8 +363,12 @@ sr_status sr_blocks_reconcile_grad(const sr_blocks_plan *plan, const void *ws, s
  * the particle with the smallest phi, ties to the smaller index.  Halo h
  * holds particles [offsets[h], offsets[h+1]) of pos [n][3] / mass [n];
  * coordinates are used as given (a halo finder's unwrapped positions).
- * Pair terms are float32; they are accumulated in float64 in groups of 8, so
- * the rounding does not grow with the halo size.  The most-bound choice is
+ * Pair terms are float32; they are accumulated in float64 in groups of at
+ * most 8, so the rounding does not grow with the halo size.  Halos of more
+ * than 256 particles evaluate every pair once, its two terms kept in float64
+ * partial sums in the workspace (8 B per particle and 256 to 4096 partners,
+ * at most 1 GiB in all; beyond that the smaller halos are summed from both
+ * ends).  The most-bound choice is
  * made on the float32 phi that is returned.  Results do not depend on the
  * launch (every sum has a fixed order). */
 typedef struct sr_centres_plan sr_centres_plan;

@@ -90,3 +90,39 @@ def test_node_catalogue_sampled():
         a, b = cat.offsets[h], cat.offsets[h + 1]
         r = oracle.halo_potential(cat.pos[a:b], cat.mass[a:b], [0, b - a], cat.eps)
         assert r[mbp[h] - a] - r.min() <= MAX_REL * abs(r.min())
+
+
+@pytest.mark.parametrize("eps", [0.02, 0.0])
+def test_pair_once_edges(eps):
+    # halos around the smallest that evaluate every pair once, the edges of target
+    # blocks (128), superblocks (256 here) and tiles (64), among one-sided ones; masses
+    # that differ, a coincident pair, and an odd one of them listed last
+    rng = np.random.default_rng(5)
+    sizes = [256, 257, 1, 320, 383, 384, 385, 0, 511, 512, 513, 640, 1023, 1024, 1025, 63, 2049, 4111]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    pos = rng.normal(size=(off[-1], 3)).astype(np.float32)
+    pos[off[9] + 500] = pos[off[9] + 3]
+    mass = rng.uniform(0.5, 2.0, off[-1]).astype(np.float32)
+    cat = synth.HaloCatalogue("edges", pos, mass, off, eps)
+    announce(f"pair-once edges n={cat.n} eps={eps}")
+    phi, mbp, pmin = run(cat)
+    ref = oracle.halo_potential(cat.pos, cat.mass, cat.offsets, eps)
+    check_phi(phi, ref, "pair-once edges")
+    check_choice(phi, mbp, pmin, cat.offsets, ref)
+    phi2, mbp2, _ = run(cat)
+    assert np.array_equal(phi.view(np.uint32), phi2.view(np.uint32)) and np.array_equal(mbp, mbp2)
+
+
+@pytest.mark.parametrize("n", [64000, 174000])
+def test_pair_once_larger_superblocks(n):
+    # catalogues large enough for superblocks of 512 and 1024 particles (windows of 512)
+    rng = np.random.default_rng(n)
+    sizes = [n, 700]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    pos = rng.normal(size=(off[-1], 3)).astype(np.float32)
+    cat = synth.HaloCatalogue("large", pos, rng.uniform(0.5, 2.0, off[-1]).astype(np.float32), off, 0.05)
+    announce(f"pair-once superblocks n={cat.n}")
+    phi, mbp, pmin = run(cat)
+    check_choice(phi, mbp, pmin, cat.offsets)
+    t = synth.sample_indices(cat.n, 3000, 4)
+    check_phi(phi[t], oracle.halo_potential(cat.pos, cat.mass, cat.offsets, cat.eps, targets=t), "superblocks")
