@@ -281,14 +281,16 @@ __global__ __launch_bounds__(64, 4) void k_centre_potential(
 // tiles of 64 sources: at step s lane l takes source (l + s) mod 64, and the
 // running sum of the opposite terms moves one lane down after the step.  Each
 // staged source serves two pairs per lane and each rotation two opposite
-// terms.  After four steps the float32 sums (four terms per target, eight per
-// source) go into float64, the targets' in registers, the sources' in LDS.
+// terms.  Every four terms the float32 sums go into float64: a target's after
+// four steps, in registers, a source's after two, in LDS (after four, eight
+// terms, it was 3% faster but a halo of some hundred particles lay 3.0e-8 from
+// the float64 sums instead of 2.7e-8 with both ends summed one by one).
 // Inside a superblock a block meets only later sources, and itself from both
 // ends.  Float64 partial sums go to rows of slots, one per partner superblock
 // (row J of particle i: its sum over superblock J; the last row: what the
 // blocks of its own superblock before its own added), and k_centre_sum adds
 // the rows in a fixed order: results are bitwise reproducible.
-// Bound by issue: 83 vector instructions (8 of them rsq) per 8 unordered pairs
+// Bound by issue: 85 vector instructions (8 of them rsq) per 8 unordered pairs
 // and lane, against 17 per pair for both ends one by one; and a halo's work is
 // cut along both axes, where an item of 128 targets walked all its sources.
 // 2,000 halos of 40 to 86,000 particles (1.65e10 ordered pairs): 7.1 -> 2.5 ms
@@ -415,26 +417,30 @@ __global__ __launch_bounds__(64, 4) void k_centre_sym(SymTables tab, uint32_t n_
                         if (base + kWave < w1) next = load_source(pos, mass, s0 + base + kWave + lane, s0 + w1);
                         const float4 *src = tile + lane;
                         double *r = red + (base - w0);
-                        int at = lane + 3;  // source whose sum the lane holds after four steps
-                        for (int s = 0; s < kWave; s += 4, at += 4) {
+                        int at = lane + 1;  // source whose sum the lane holds after two steps
+                        for (int s = 0; s < kWave; s += 4) {
                             float ga = 0.f, gb = 0.f, b = 0.f;
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
                                 const float4 sj = src[s + u];
                                 const float qa = pair_q<kSoft>(sj, ta.x, ta.y, ta.z, eps2);
                                 const float qb = pair_q<kSoft>(sj, tb.x, tb.y, tb.z, eps2);
-                                if (u > 0) b = lane_down(b);
+                                if (u & 1) b = lane_down(b);
                                 ga = fmaf(sj.w, qa, ga);
                                 gb = fmaf(sj.w, qb, gb);
                                 b = fmaf(ta.w, qa, b);
                                 b = fmaf(tb.w, qb, b);
+                                if (u & 1) {
+                                    // an LDS atomic, since other lanes add to the entry before and after;
+                                    // one lane per entry and instruction, so the order of sums is fixed
+                                    __hip_atomic_fetch_add(&r[at & (kWave - 1)], (double)b, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                                    b = 0.f;
+                                    at += 2;
+                                }
                             }
                             acc_a += (double)ga;
                             acc_b += (double)gb;
-                            // an LDS atomic, since other lanes add to the entry before and after; one
-                            // lane per entry and instruction, so the order of sums is fixed
-                            __hip_atomic_fetch_add(&r[at & (kWave - 1)], (double)b, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
                         }
                     }
                 }
