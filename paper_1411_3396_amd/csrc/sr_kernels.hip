@@ -225,9 +225,15 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const int *__restrict__ in,
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// out[i] = offs[block] + sum_{k<i in block} in[k]; the last block also writes out[m].
+// out[i] = sum_{k<i} in[k]; the last block also writes out[m].  A block finds
+// what comes before it by itself: from the blocks' sums (kSums), or, for a
+// short array, from the array.
+constexpr int kScanAlone = 16;   // blocks that read the array itself (128 KB at most)
+constexpr int kScanSums = 2048;  // blocks that read the sums (8 KB)
+
+template <bool kSums>
 __global__ __launch_bounds__(256) void k_scan_apply(const int *__restrict__ in, int64_t m,
-                                                    const int *__restrict__ offs,
+                                                    const int *__restrict__ before,
                                                     int *__restrict__ out)
 {
     __shared__ int lds[4];
@@ -239,35 +245,67 @@ __global__ __launch_bounds__(256) void k_scan_apply(const int *__restrict__ in, 
         v[k] = (base + k < m) ? in[base + k] : 0;
         s += v[k];
     }
-    int total;
-    int run = block_excl_scan(s, total, lds) + (offs ? offs[blockIdx.x] : 0);
+    int prior = 0;
+    const int np = kSums ? (int)blockIdx.x : (int)blockIdx.x * kScanBlock;
+#pragma unroll 8
+    for (int k = threadIdx.x; k < np; k += 256) prior += before[k];
+    int offs, total;
+    block_excl_scan(prior, offs, lds);
+    int run = block_excl_scan(s, total, lds) + offs;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (base + k < m) out[base + k] = run;
         run += v[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-        out[m] = (offs ? offs[blockIdx.x] : 0) + total;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[m] = offs + total;
+}
+
+// out[i] = offs[block] + sum_{k<i in block} in[k] (arrays whose block sums are scanned first).
+__global__ __launch_bounds__(256) void k_scan_add(const int *__restrict__ in, int64_t m,
+                                                  const int *__restrict__ offs, int *__restrict__ out)
+{
+    __shared__ int lds[4];
+    const int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
+    int v[kScanItems];
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        v[k] = (base + k < m) ? in[base + k] : 0;
+        s += v[k];
+    }
+    int total;
+    int run = block_excl_scan(s, total, lds) + offs[blockIdx.x];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        if (base + k < m) out[base + k] = run;
+        run += v[k];
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[m] = offs[blockIdx.x] + total;
 }
 
 // Exclusive scan of in[0..m) into out[0..m] (out[m] = total).  tmp holds
-// scan_scratch_elems(m) ints.
+// scan_scratch_elems(m) ints.  A dependent launch costs some 4.5 us, so a
+// scan takes one launch up to kScanAlone blocks of 2048, two up to kScanSums.
 hipError_t scan_i32(const int *in, int *out, int64_t m, int *tmp, hipStream_t st)
 {
-    const int64_t nb = (m + kScanBlock - 1) / kScanBlock;
-    if (nb <= 1) {
-        k_scan_apply<<<1, 256, 0, st>>>(in, m, nullptr, out);
+    const int64_t nb = std::max<int64_t>(1, (m + kScanBlock - 1) / kScanBlock);
+    if (nb <= kScanAlone) {
+        k_scan_apply<false><<<(unsigned)nb, 256, 0, st>>>(in, m, in, out);
         return hipGetLastError();
     }
     int *sums = tmp;
-    int *sums_x = tmp + nb;
-    int *next = sums_x + nb + 1;
     k_scan_reduce<<<(unsigned)nb, 256, 0, st>>>(in, m, sums);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (nb <= kScanSums) {
+        k_scan_apply<true><<<(unsigned)nb, 256, 0, st>>>(in, m, sums, out);
+        return hipGetLastError();
+    }
+    int *sums_x = tmp + nb;
+    int *next = sums_x + nb + 1;
     e = scan_i32(sums, sums_x, nb, next, st);
     if (e != hipSuccess) return e;
-    k_scan_apply<<<(unsigned)nb, 256, 0, st>>>(in, m, sums_x, out);
+    k_scan_add<<<(unsigned)nb, 256, 0, st>>>(in, m, sums_x, out);
     return hipGetLastError();
 }
 

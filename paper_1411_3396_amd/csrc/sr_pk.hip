@@ -67,14 +67,6 @@ __global__ __launch_bounds__(256) void k_cic_key(const float *__restrict__ pos,
     pf[i] = make_float4(f[0], f[1], f[2], mass[i]);
 }
 
-__global__ __launch_bounds__(256) void k_cic_pack(const int *__restrict__ perm, int n,
-                                                  const float4 *__restrict__ pf,
-                                                  float4 *__restrict__ spf)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) spf[i] = pf[perm[i]];
-}
-
 // Sorted deposit, step 2: each particle's 8 corner contributions
 // m w_x w_y w_z (float products, widened to float64), summed over the runs of
 // equal cells inside each 64-slot wave of the sorted order by a segmented
@@ -82,15 +74,15 @@ __global__ __launch_bounds__(256) void k_cic_pack(const int *__restrict__ perm, 
 // k = 4 c_x + 2 c_y + c_z for the corner point (lower corner + (c_x, c_y, c_z)).
 // A cell's particles thus end up as one partial per wave they touch, stored
 // at the wave's last slot inside the cell and at the cell's last slot.
-__global__ __launch_bounds__(256) void k_cic_runs(const int *__restrict__ skey,
-                                                  const float4 *__restrict__ spf, int n,
+__global__ __launch_bounds__(256) void k_cic_runs(const int *__restrict__ skey, const int *__restrict__ perm,
+                                                  const float4 *__restrict__ pf, int n,
                                                   double *__restrict__ seg)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const bool valid = i < n;
     const int key = valid ? skey[i] : -1;
-    const float4 v = valid ? spf[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 v = valid ? pf[perm[i]] : make_float4(0.f, 0.f, 0.f, 0.f);
     double c[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -119,15 +111,48 @@ __global__ __launch_bounds__(256) void k_cic_runs(const int *__restrict__ skey,
     }
 }
 
+// Float64 sum of the masses: strided partial sums per thread, a fixed tree
+// per workgroup, then one workgroup over the partials.
+__device__ __forceinline__ double block_sum(double v, double *lds)
+{
+    lds[threadIdx.x] = v;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
+        __syncthreads();
+    }
+    return lds[0];
+}
+
+__global__ __launch_bounds__(256) void k_mass_partial(const float *__restrict__ mass, int n,
+                                                      double *__restrict__ part)
+{
+    __shared__ double lds[256];
+    double v = 0.0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) v += (double)mass[i];
+    const double s = block_sum(v, lds);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+__device__ __forceinline__ void mass_final(const double *__restrict__ part, int parts, double *__restrict__ total)
+{
+    __shared__ double lds[256];
+    double v = 0.0;
+    for (int i = threadIdx.x; i < parts; i += 256) v += part[i];
+    const double s = block_sum(v, lds);
+    if (threadIdx.x == 0) total[0] = s;
+}
+
 // Sorted deposit, step 3: every grid point adds, in float64 and a fixed order,
 // the partials of the 8 cells whose lower corner is the point or its lower
 // neighbours (cells (p - c) for c in {0,1}^3, periodic): for a cell of slots
 // [a, b), the partials at the last slot of each 64-slot wave below b - 1, then
-// at b - 1.
+// at b - 1.  Workgroup 0 also adds up the mass sum's partials.
 __global__ __launch_bounds__(256) void k_cic_points(const int *__restrict__ cstart,
                                                     const double *__restrict__ seg, int ng, int pad,
-                                                    float *__restrict__ grid)
+                                                    float *__restrict__ grid, double *__restrict__ mpart)
 {
+    if (blockIdx.x == 0) mass_final(mpart, kSumBlocks, mpart + kSumBlocks);
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t total = (int64_t)ng * ng * ng;
     if (g >= total) return;
@@ -224,16 +249,15 @@ __device__ __forceinline__ void brick_of(const float (&x)[3], float m, int ng, f
     v = make_float4(lu[0], lu[1], lu[2], m);
 }
 
-// Keys and payloads of one tile of kRadixTile particles, the first sort
-// pass's digit counts of the tile (table[d * ntiles + tile]), and the tile's
-// float64 mass sum (a fixed order per thread, then a fixed tree) and largest
-// |m|.
+// The first sort pass's digit counts of one tile of kRadixTile particles
+// (table[d * ntiles + tile]), and the tile's float64 mass sum (a fixed order
+// per thread, then a fixed tree) and largest |m|.  Keys and payloads are not
+// kept: that pass's scatter makes them again from the same inputs, which
+// spares 20 B written and 4 B read per particle.
 __global__ __launch_bounds__(kSortThreads) void k_brick_hist0(const float *__restrict__ pos,
                                                               const float *__restrict__ mass, int n,
                                                               int ng, float inv_h, int bits,
                                                               int *__restrict__ table, int ntiles,
-                                                              int *__restrict__ keys,
-                                                              float4 *__restrict__ vals,
                                                               double *__restrict__ msum,
                                                               float *__restrict__ mmax)
 {
@@ -268,8 +292,6 @@ __global__ __launch_bounds__(kSortThreads) void k_brick_hist0(const float *__res
             float4 v;
             const float x[3] = {lp[3 * e], lp[3 * e + 1], lp[3 * e + 2]};
             brick_of(x, mass[i], ng, inv_h, key, v);
-            keys[i] = key;
-            vals[i] = v;
             atomicAdd(&h[key & (R - 1)], 1);
             s += (double)v.w;
             mx = fmaxf(mx, fabsf(v.w));
@@ -338,7 +360,11 @@ __global__ __launch_bounds__(kSortThreads) void k_brick_hist(const int *__restri
 // their digit (one ballot per digit bit, per-wave digit counters), the tile is
 // reordered by digit in LDS keeping input order inside a digit, and each
 // digit's run is written to consecutive addresses from the scanned table.
+// With kFirst (the first pass) keys and payloads come from positions and
+// masses.
+template <bool kFirst>
 __global__ __launch_bounds__(kSortThreads) void k_brick_scatter(
+    const float *__restrict__ pos, const float *__restrict__ mass, int ng, float inv_h,
     const int *__restrict__ keys_in, const float4 *__restrict__ v_in, int n, int shift, int bits,
     const int *__restrict__ table_x, int ntiles, int *__restrict__ keys_out, float4 *__restrict__ v_out)
 {
@@ -373,8 +399,13 @@ __global__ __launch_bounds__(kSortThreads) void k_brick_scatter(
         key[r] = 0;
         v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (valid) {
-            key[r] = keys_in[e];
-            v[r] = v_in[e];
+            if constexpr (kFirst) {
+                const float x[3] = {pos[3 * e], pos[3 * e + 1], pos[3 * e + 2]};
+                brick_of(x, mass[e], ng, inv_h, key[r], v[r]);
+            } else {
+                key[r] = keys_in[e];
+                v[r] = v_in[e];
+            }
         }
         const int d = (key[r] >> shift) & (R - 1);
         uint64_t peers = __ballot(valid);
@@ -661,39 +692,6 @@ __global__ __launch_bounds__(256) void k_brick_combine(const int *__restrict__ c
     for (int k = 0; k < kBrick; ++k) g[k] = (float)sum[k];
 }
 
-// Float64 sum of the masses: strided partial sums per thread, a fixed tree
-// per workgroup, then one workgroup over the partials.
-__device__ __forceinline__ double block_sum(double v, double *lds)
-{
-    lds[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
-        __syncthreads();
-    }
-    return lds[0];
-}
-
-__global__ __launch_bounds__(256) void k_mass_partial(const float *__restrict__ mass, int n,
-                                                      double *__restrict__ part)
-{
-    __shared__ double lds[256];
-    double v = 0.0;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) v += (double)mass[i];
-    const double s = block_sum(v, lds);
-    if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-__global__ __launch_bounds__(256) void k_mass_final(const double *__restrict__ part, int parts,
-                                                    double *__restrict__ total)
-{
-    __shared__ double lds[256];
-    double v = 0.0;
-    for (int i = threadIdx.x; i < parts; i += 256) v += part[i];
-    const double s = block_sum(v, lds);
-    if (threadIdx.x == 0) total[0] = s;
-}
-
 // Modes of the half spectrum (iz in [0, ng/2]).  Each wave of a workgroup
 // takes whole rows (ix, iy) in a fixed order and keeps its own bins in LDS.
 // Along a row |n| grows with iz, so each bin is one run of consecutive modes.
@@ -708,12 +706,20 @@ __global__ __launch_bounds__(256) void k_mass_final(const double *__restrict__ p
 // bins are then added in wave order and written transposed,
 // part[(3 b + j) blocks + workgroup], for the last pass.  The sums therefore do
 // not depend on scheduling: the spectrum is bitwise reproducible.
-// iw[i] = 1 / sinc^4(pi n_i / ng) for the mode index n_i of array index i.
+// iw[i] = 1 / sinc^4(pi n_i / ng) for the mode index n_i of array index i,
+// made by every workgroup in LDS (8 KB at the largest grid).
 __global__ __launch_bounds__(256) void k_pk_bins(const float2 *__restrict__ c, int ng, int n_bins,
-                                                 double inv_dn, const double *__restrict__ iw,
-                                                 double *__restrict__ part)
+                                                 double inv_dn, double *__restrict__ part)
 {
-    extern __shared__ double bins[];  // per wave [3][n_bins]: sum of w P', sum of w |n|, sum of w
+    extern __shared__ double iw[];  // [ng], then the bins
+    double *bins = iw + ng;  // per wave [3][n_bins]: sum of w P', sum of w |n|, sum of w
+    for (int i = threadIdx.x; i < ng; i += blockDim.x) {
+        const int nm = i <= ng / 2 ? i : i - ng;
+        const double x = 3.14159265358979323846 * nm / ng;
+        const double q = nm == 0 ? 1.0 : sin(x) / x;
+        const double q2 = q * q;
+        iw[i] = 1.0 / (q2 * q2);
+    }
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
     const int nb3 = 3 * n_bins;
@@ -854,20 +860,9 @@ __global__ __launch_bounds__(256) void k_pk_final(const double *__restrict__ par
     if (modes) modes[b] = (int64_t)(sw + 0.5);
 }
 
-// iw[i] = 1 / sinc^4(pi n / ng) for the mode index n of array index i.
-__global__ __launch_bounds__(256) void k_pk_sinc(int ng, double *__restrict__ iw)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= ng) return;
-    const int nm = i <= ng / 2 ? i : i - ng;
-    const double x = 3.14159265358979323846 * nm / ng;
-    const double s = nm == 0 ? 1.0 : sin(x) / x;
-    const double s2 = s * s;
-    iw[i] = 1.0 / (s2 * s2);
-}
-
-// Waves per workgroup of the binning: up to 4, as many as their bins fit 64 KiB of LDS.
-int bin_waves(int n_bins) { return std::max(1, std::min(4, 65536 / (24 * n_bins))); }
+// Waves per workgroup of the binning: up to 4, as many as their bins fit 64 KiB of LDS beside
+// the window table (one always does: at most 48 KiB and 8 KiB).
+int bin_waves(int n_bins, int ng) { return std::max(1, std::min(4, (65536 - 8 * ng) / (24 * n_bins))); }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -886,7 +881,7 @@ struct sr_pk_plan {
     int64_t tiles = 1;
     bool brick = false;      // brick deposit (ng a multiple of 8), else the cell deposit
     int64_t nbricks = 0, max_chunks = 0;
-    size_t grid_off = 0, grid_bytes = 0, sinc_off = 0, mass_off = 0, part_off = 0, work_off = 0,
+    size_t grid_off = 0, grid_bytes = 0, mass_off = 0, part_off = 0, work_off = 0,
            key_off[2] = {0, 0}, val_off[2] = {0, 0}, pf_off = 0, spf_off = 0, seg_off = 0, cstart_off = 0,
            tab_off = 0, tabx_off = 0, scan_off = 0, chunks_off = 0, cbase_off = 0, owner_off = 0,
            ctile_off = 0, msum_off = 0, mmax_off = 0, ws_bytes = 0;
@@ -945,10 +940,8 @@ sr_status deposit_bricks(sr_pk_plan *P, const float *pos, const float *mass, int
         const int tiles = (int)((n + kRadixTile - 1) / kRadixTile);
         double *msum = reinterpret_cast<double *>(w + P->msum_off);
         float *mmax = reinterpret_cast<float *>(w + P->mmax_off);
-        // keys and payloads (with the first pass's digit counts) into buffer
-        // passes & 1, then a stable radix sort by brick moving the payloads
-        // with the keys; pass p reads buffer (passes + p) & 1 and writes the
-        // other, so the last lands in buffer 0
+        // a stable radix sort by brick moving the payloads with the keys; pass
+        // p writes buffer (passes + p + 1) & 1, so the last lands in buffer 0
         auto K = [&](int q) { return I(P->key_off[q]); };
         auto Vb = [&](int q) { return V(q ? P->spf_off : P->pf_off); };
         const int first = P->passes & 1;
@@ -960,15 +953,21 @@ sr_status deposit_bricks(sr_pk_plan *P, const float *pos, const float *mass, int
             const int in = (first + p) & 1, out = in ^ 1;
             if (p == 0)
                 k_brick_hist0<<<tiles, kSortThreads, 0, s>>>(pos, mass, (int)n, P->ng, inv_h, bits,
-                                                             I(P->tab_off), tiles, K(in), Vb(in), msum, mmax);
+                                                             I(P->tab_off), tiles, msum, mmax);
             else
                 k_brick_hist<<<tiles, kSortThreads, 0, s>>>(K(in), (int)n, shift, bits, I(P->tab_off),
                                                             tiles);
             if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
             if (dev_scan(I(P->tab_off), I(P->tabx_off), (int64_t)R * tiles, I(P->scan_off), s) != hipSuccess)
                 return SR_E_DEVICE;
-            k_brick_scatter<<<tiles, kSortThreads, 0, s>>>(K(in), Vb(in), (int)n, shift, bits,
-                                                           I(P->tabx_off), tiles, K(out), Vb(out));
+            if (p == 0)
+                k_brick_scatter<true><<<tiles, kSortThreads, 0, s>>>(pos, mass, P->ng, inv_h, nullptr, nullptr,
+                                                                     (int)n, shift, bits, I(P->tabx_off), tiles,
+                                                                     K(out), Vb(out));
+            else
+                k_brick_scatter<false><<<tiles, kSortThreads, 0, s>>>(nullptr, nullptr, 0, 0.f, K(in), Vb(in),
+                                                                      (int)n, shift, bits, I(P->tabx_off), tiles,
+                                                                      K(out), Vb(out));
             if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
         }
         k_brick_bounds<<<(unsigned)((n / 4 + 1 + 255) / 256), 256, 0, s>>>(K(0), (int)n, nbricks, bstart);
@@ -1007,7 +1006,6 @@ sr_status deposit(sr_pk_plan *P, const float *pos, const float *mass, int64_t n,
     {
         const int64_t cells = (int64_t)P->ng * P->ng * P->ng;
         float4 *pf = reinterpret_cast<float4 *>(w + P->pf_off);
-        float4 *spf = reinterpret_cast<float4 *>(w + P->spf_off);
         double *seg = reinterpret_cast<double *>(w + P->seg_off);
         if (n > 0) {
             k_cic_key<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(pos, mass, (int)n, P->ng, inv_h,
@@ -1021,21 +1019,19 @@ sr_status deposit(sr_pk_plan *P, const float *pos, const float *mass, int64_t n,
                 hipSuccess)
                 return SR_E_DEVICE;
             const int out = (P->passes - 1) & 1;
-            k_cic_pack<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(I(P->val_off[out]), (int)n, pf, spf);
-            if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
             if (dev_bounds(I(P->key_off[out]), n, cells, 0, I(P->cstart_off), s) != hipSuccess)
                 return SR_E_DEVICE;
-            k_cic_runs<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(I(P->key_off[out]), spf, (int)n, seg);
+            k_cic_runs<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(I(P->key_off[out]), I(P->val_off[out]), pf, (int)n,
+                                                                  seg);
             if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
         } else if (dev_zero(I(P->cstart_off), cells + 1, s) != hipSuccess) {
             return SR_E_DEVICE;
         }
-        k_cic_points<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(I(P->cstart_off), seg, P->ng, pad, grid);
+        double *part = reinterpret_cast<double *>(w + P->mass_off);
+        k_mass_partial<<<kSumBlocks, 256, 0, s>>>(mass, (int)n, part);
         if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
+        k_cic_points<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(I(P->cstart_off), seg, P->ng, pad, grid, part);
     }
-    double *part = reinterpret_cast<double *>(w + P->mass_off);
-    k_mass_partial<<<kSumBlocks, 256, 0, s>>>(mass, (int)n, part);
-    k_mass_final<<<1, 256, 0, s>>>(part, kSumBlocks, part + kSumBlocks);
     return hipGetLastError() == hipSuccess ? SR_OK : SR_E_DEVICE;
 }
 
@@ -1063,8 +1059,6 @@ sr_status sr_pk_plan_create(int32_t ng, double box, int32_t n_bins, double dn, i
     size_t o = 0;
     P->grid_off = o;
     o = align256(o + P->grid_bytes);
-    P->sinc_off = o;
-    o = align256(o + sizeof(double) * ng);
     P->mass_off = o;
     o = align256(o + sizeof(double) * (kSumBlocks + 2));
     P->part_off = o;
@@ -1133,8 +1127,6 @@ sr_status sr_pk_plan_create(int32_t ng, double box, int32_t n_bins, double dn, i
         }
         P->pf_off = o;
         o = align256(o + sizeof(float4) * m);
-        P->spf_off = o;
-        o = align256(o + sizeof(float4) * m);
         P->seg_off = o;
         o = align256(o + sizeof(double) * 8 * m);
         P->cstart_off = o;
@@ -1193,8 +1185,6 @@ sr_status sr_power_spectrum(sr_pk_plan *P, const float *pos, const float *mass, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *w = static_cast<char *>(ws);
     if ((st = deposit(P, pos, mass, n, w, s)) != SR_OK) return st;
-    k_pk_sinc<<<(unsigned)((P->ng + 255) / 256), 256, 0, s>>>(P->ng, reinterpret_cast<double *>(w + P->sinc_off));
-    if (hipGetLastError() != hipSuccess) return SR_E_DEVICE;
     rocfft_execution_info info = nullptr;
     if (rocfft_execution_info_create(&info) != rocfft_status_success) return SR_E_DEVICE;
     bool ok = rocfft_execution_info_set_stream(info, s) == rocfft_status_success &&
@@ -1205,10 +1195,9 @@ sr_status sr_power_spectrum(sr_pk_plan *P, const float *pos, const float *mass, 
     (void)rocfft_execution_info_destroy(info);
     if (!ok) return SR_E_DEVICE;
     double *part = reinterpret_cast<double *>(w + P->part_off);
-    const int nw = bin_waves(P->n_bins);
-    k_pk_bins<<<kBinBlocks, nw * kWave, sizeof(double) * 3 * nw * P->n_bins, s>>>(
-        reinterpret_cast<const float2 *>(w + P->grid_off), P->ng, P->n_bins, 1.0 / P->dn,
-        reinterpret_cast<const double *>(w + P->sinc_off), part);
+    const int nw = bin_waves(P->n_bins, P->ng);
+    k_pk_bins<<<kBinBlocks, nw * kWave, sizeof(double) * (P->ng + 3 * nw * P->n_bins), s>>>(
+        reinterpret_cast<const float2 *>(w + P->grid_off), P->ng, P->n_bins, 1.0 / P->dn, part);
     k_pk_final<<<(unsigned)P->n_bins, 256, 0, s>>>(
         part, kBinBlocks, P->n_bins, reinterpret_cast<const double *>(w + P->mass_off) + kSumBlocks, P->box,
         pk, k, modes);
