@@ -357,6 +357,7 @@ sr_status device_args(DevArgs &a, void *ws, const Layout *L, const SegParams *se
     a.sym_balance = g_sym_balance.load();
     a.sparse_group = g_sparse_group.load();
     a.pull_limit = pull_limit();
+    a.just_binned = false;
     return SR_OK;
 }
 
@@ -461,6 +462,7 @@ sr_status run_batched(sr_batch_plan *P, const float *pos, const float *mass, voi
                                   sizeof(SegParams) * P->B, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return SR_E_DEVICE;
     if ((e = dev_bin(a, pos, mass)) != hipSuccess) return SR_E_DEVICE;
+    a.just_binned = true;
     if (P->total_active > 0 && (e = dev_force(a, acc)) != hipSuccess) return SR_E_DEVICE;
     if (mom && (e = dev_momentum(a, acc, mass, mom)) != hipSuccess) return SR_E_DEVICE;
     return SR_OK;
@@ -486,6 +488,7 @@ sr_status run_per_subvolume(sr_batch_plan *P, const float *pos, const float *mas
         a.sym_rounds = 1;
         if (n > 0) {
             if (dev_bin(a, pos + 3 * off, mass + off) != hipSuccess) return SR_E_DEVICE;
+            a.just_binned = true;
             if (P->n_active[b] > 0 && dev_force(a, acc + 3 * out_off) != hipSuccess) return SR_E_DEVICE;
         }
         if (mom) {
@@ -798,7 +801,10 @@ sr_status sr_force(const float *pos, const float *mass, int64_t n, int64_t n_act
     sym_tail(s.L, ws_bytes);  // the whole tail of the caller's workspace holds partial slots
     DevArgs a;
     if ((st = device_args(a, ws, &s.L, &s.seg, nullptr, stream, 0, n_active)) != SR_OK) return st;
-    if (!(flags & SR_REUSE_BINS) && dev_bin(a, pos, mass) != hipSuccess) return SR_E_DEVICE;
+    if (!(flags & SR_REUSE_BINS)) {
+        if (dev_bin(a, pos, mass) != hipSuccess) return SR_E_DEVICE;
+        a.just_binned = true;
+    }
     if (n_active == 0) return SR_OK;
     return hip_status(dev_force(a, acc));
 }

@@ -68,6 +68,7 @@ enum HdrWord : int {
     kHdrNItems = 1,
     kHdrMagic = 2,          // written by the last binning kernel: bins are ready
     kHdrMassInfo = 3,       // 0 if every mass equals the first one
+    kHdrLists = 64,         // the work lists' words: counters, decisions, queues (to the end)
     kHdrBucketCount = 64,   // [32]
     kHdrBucketCursor = 192, // [32]
     kHdrQueue = 256,        // queue q at kHdrQueue + 32*q (separate 128-byte lines)
@@ -153,6 +154,7 @@ struct DevArgs {
     double sym_balance;    // symmetric tiles: how well their items must spread over the waves (0: one fixed shape)
     int sparse_group;      // most targets per item of a cell (or remainder) with fewer than 64: 8, 16, 32 or 64
     int64_t pull_limit;    // most items one wave of a persistent kernel may pull (test hook)
+    bool just_binned;      // dev_bin ran right before on this workspace: the work lists' header words are zero
 };
 
 hipError_t dev_bin(const DevArgs &a, const float *pos, const float *mass);

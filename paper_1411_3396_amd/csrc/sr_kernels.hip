@@ -606,8 +606,11 @@ __global__ __launch_bounds__(256) void k_gather_g(int N, int n_rows,
                                                   const int *__restrict__ out_row,
                                                   const float *__restrict__ g,
                                                   float *__restrict__ gx, float *__restrict__ gy,
-                                                  float *__restrict__ gz)
+                                                  float *__restrict__ gz, uint32_t *hdr)
 {
+    // the work lists' counters, for the kernels after this one
+    if (blockIdx.x == 0)
+        for (int i = kHdrLists + threadIdx.x; i < kHdrWords; i += 256) hdr[i] = 0u;
     const int b = blockIdx.x * 256 + threadIdx.x;
     if (b >= N) return;
     const int r = out_row[b];
@@ -847,15 +850,18 @@ struct PullGuard {
 struct ItemQueue {
     uint32_t *counters;  // queue q at counters[32 q]
     uint32_t n;          // items (below 2^31, and so are the items a few counter steps past the end)
+    uint32_t wave;       // this wave's number among `waves`
     int turn = 0;        // queues done
     bool single;         // one item per wave at most
     PullGuard guard;
-    __device__ __forceinline__ ItemQueue(uint32_t *hdr, int qbase, uint32_t items, int64_t pull_limit)
-        : counters(hdr + qbase), n(items), single(items <= (gridDim.x & ~(unsigned)(kQueues * kQueueBlock - 1))),
+    __device__ __forceinline__ ItemQueue(uint32_t *hdr, int qbase, uint32_t items, int64_t pull_limit,
+                                         uint32_t wave_, uint32_t waves)
+        : counters(hdr + qbase), n(items), wave(wave_),
+          single(items <= (waves & ~(unsigned)(kQueues * kQueueBlock - 1))),
           guard((uint32_t)min((int64_t)items, pull_limit))
     {
     }
-    __device__ __forceinline__ int queue() const { return (int)(blockIdx.x + turn) & (kQueues - 1); }
+    __device__ __forceinline__ int queue() const { return (int)(wave + turn) & (kQueues - 1); }
     __device__ __forceinline__ uint32_t item(uint32_t c) const
     {
         return ((c / kQueueBlock) * kQueues + queue()) * kQueueBlock + (c % kQueueBlock);
@@ -865,7 +871,7 @@ struct ItemQueue {
     {
         if (single) {
             if (turn > 0) return false;
-            g = item(blockIdx.x / kQueues);
+            g = item(wave / kQueues);
             turn = 1;
             return g < n && guard.accept(g);
         }
@@ -1122,11 +1128,11 @@ __device__ __forceinline__ void force_items(const Acc &acc, const int4 *__restri
                                             const int *__restrict__ nact,
                                             const Src &src, const int *__restrict__ out_row,
                                             float *__restrict__ out, int n_out, float4 *stage,
-                                            int64_t pull_limit)
+                                            int64_t pull_limit, uint32_t wave, uint32_t waves)
 {
     const int lane = threadIdx.x;
     const float m0 = kUM ? src.m[0] : 1.0f;
-    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit);
+    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit, wave, waves);
     for (uint32_t g; queue.next(lane, g);) {
         const int4 it = load_item(items, g);
         const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
@@ -1215,9 +1221,9 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_force(
 {
     __shared__ float4 stage[kStageForce + kWave];
     if (hdr[kHdrMassInfo] == 0)
-        force_items<Acc, kSoft, true>(acc, items, hdr, start, nact, src, out_row, out, n_out, stage, pull_limit);
+        force_items<Acc, kSoft, true>(acc, items, hdr, start, nact, src, out_row, out, n_out, stage, pull_limit, blockIdx.x, gridDim.x);
     else
-        force_items<Acc, kSoft, false>(acc, items, hdr, start, nact, src, out_row, out, n_out, stage, pull_limit);
+        force_items<Acc, kSoft, false>(acc, items, hdr, start, nact, src, out_row, out, n_out, stage, pull_limit, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------------- adjoint kernel
@@ -1234,12 +1240,12 @@ __device__ __forceinline__ void vjp_items(const Acc &acc, const int4 *__restrict
                                           const float *__restrict__ gz,
                                           const int *__restrict__ perm, float *__restrict__ out,
                                           int n_out, float4 *stage_p, float4 *stage_g,
-                                          int64_t pull_limit)
+                                          int64_t pull_limit, uint32_t wave, uint32_t waves)
 {
     const int lane = threadIdx.x;
     // the common mass (or 1), times -3: the pair sums are at the scale -1/3
     const float m0 = -3.0f * (kUM ? src.m[0] : 1.0f);
-    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit);
+    ItemQueue queue(hdr, kHdrQueue, hdr[kHdrNItems], pull_limit, wave, waves);
     for (uint32_t g; queue.next(lane, g);) {
         const int4 it = load_item(items, g);
         const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
@@ -1344,10 +1350,10 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_vjp(
     __shared__ float4 stage_g[kStageVjp + kWave];
     if (hdr[kHdrMassInfo] == 0)
         vjp_items<Acc, kSoft, true>(acc, items, hdr, start, nact, src, gx, gy, gz, perm, out, n_out,
-                                    stage_p, stage_g, pull_limit);
+                                    stage_p, stage_g, pull_limit, blockIdx.x, gridDim.x);
     else
         vjp_items<Acc, kSoft, false>(acc, items, hdr, start, nact, src, gx, gy, gz, perm, out, n_out,
-                                     stage_p, stage_g, pull_limit);
+                                     stage_p, stage_g, pull_limit, blockIdx.x, gridDim.x);
 }
 
 // Ordered pairs (target, source) with 0 < s < r_s^2 over the items of one
@@ -1364,7 +1370,7 @@ __global__ __launch_bounds__(64) void k_count(Acc acc, const int4 *__restrict__ 
     const int lane = threadIdx.x;
     const uint32_t n_items = hdr[kHdrNItems];
     unsigned long long pairs = 0;
-    ItemQueue queue(hdr, kHdrQueue, n_items, pull_limit);
+    ItemQueue queue(hdr, kHdrQueue, n_items, pull_limit, blockIdx.x, gridDim.x);
     for (uint32_t g; queue.next(lane, g);) {
         const int4 it = load_item(items, g);
         const int t0 = it.y, nt = it.z, lk = item_lk(it.w);
@@ -2201,7 +2207,8 @@ __device__ __forceinline__ void force_sym_items(const Acc &acc, const int4 *__re
                                                 const int *__restrict__ sym_base,
                                                 const int *__restrict__ sym_pref, const Src &src,
                                                 float *__restrict__ pool, float4 *tile,
-                                                int *tix, SymRed<kW> &red, int64_t pull_limit)
+                                                int *tix, SymRed<kW> &red, int64_t pull_limit,
+                                                uint32_t wave, uint32_t waves)
 {
     const int lane = threadIdx.x;
     const uint32_t n_items = hdr[kHdrSymNItems];
@@ -2209,7 +2216,7 @@ __device__ __forceinline__ void force_sym_items(const Acc &acc, const int4 *__re
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
     const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
-    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit);
+    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit, wave, waves);
     for (uint32_t gi; queue.next(lane, gi);) {
         const int4 it = load_item(items, gi);
         const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
@@ -2366,10 +2373,10 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_force_sym(Acc acc, 
     __shared__ SymRed<kW> red;
     if (hdr[kHdrMassInfo] == 0)
         force_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool,
-                                              tile, tix, red, pull_limit);
+                                              tile, tix, red, pull_limit, blockIdx.x, gridDim.x);
     else
         force_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, pool,
-                                               tile, tix, red, pull_limit);
+                                               tile, tix, red, pull_limit, blockIdx.x, gridDim.x);
 }
 
 // Adjoint symmetric items: as the forward, with the cotangent staged beside
@@ -2383,7 +2390,8 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
                                               const float *__restrict__ gx, const float *__restrict__ gy,
                                               const float *__restrict__ gz, float *__restrict__ pool,
                                               float4 *tile_p, float4 *tile_g, int *tix,
-                                              SymRed<kW> &red, int64_t pull_limit)
+                                              SymRed<kW> &red, int64_t pull_limit, uint32_t wave,
+                                              uint32_t waves)
 {
     const int lane = threadIdx.x;
     const uint32_t n_items = hdr[kHdrSymNItems];
@@ -2391,7 +2399,7 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
     // thousands of idle waves would otherwise all hit once per queue
     if (n_items == 0) return;
     const int K = (int)hdr[kHdrSymK], R = (int)hdr[kHdrSymR];
-    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit);
+    ItemQueue queue(hdr, kHdrSymQueue, n_items, pull_limit, wave, waves);
     for (uint32_t gi; queue.next(lane, gi);) {
         const int4 it = load_item(items, gi);
         const int c = it.x, g = it.y, kk = it.z;  // kk: the item's group of R windows
@@ -2536,8 +2544,8 @@ __device__ __forceinline__ void vjp_sym_items(const Acc &acc, const int4 *__rest
     queue.guard.report(hdr, lane);
 }
 
-template <class Acc, bool kSoft, int kW, int kOcc>
-__global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_vjp_sym(Acc acc, const int4 *__restrict__ items, uint32_t *hdr,
+template <class Acc, bool kSoft, int kW>
+__global__ __launch_bounds__(64) void k_vjp_sym(Acc acc, const int4 *__restrict__ items, uint32_t *hdr,
                                                 const int *__restrict__ start,
                                                 const int *__restrict__ nact,
                                                 const int *__restrict__ sym_base,
@@ -2552,10 +2560,91 @@ __global__ __launch_bounds__(64, kOcc > 0 ? kOcc : 1) void k_vjp_sym(Acc acc, co
     __shared__ SymRed<kW> red;
     if (hdr[kHdrMassInfo] == 0)
         vjp_sym_items<Acc, kSoft, true, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool,
-                                            tile_p, tile_g, tix, red, pull_limit);
+                                            tile_p, tile_g, tix, red, pull_limit, blockIdx.x, gridDim.x);
     else
         vjp_sym_items<Acc, kSoft, false, kW>(acc, items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz, pool,
-                                             tile_p, tile_g, tix, red, pull_limit);
+                                             tile_p, tile_g, tix, red, pull_limit, blockIdx.x, gridDim.x);
+}
+
+// Both kinds of items in one launch: workgroups [0, sym_waves) take the
+// symmetric ones (windows of 256), the others the one-sided ones.  Neither
+// waits for the other, so the end of the one overlaps the start of the other,
+// and a problem without dense particles pays for one launch less.
+template <class Acc, bool kSoft>
+__global__ __launch_bounds__(64, 1) void k_force_both(
+    Acc acc, const int4 *__restrict__ items, const int4 *__restrict__ sym_items, uint32_t *hdr,
+    const int *__restrict__ start, const int *__restrict__ nact, const int *__restrict__ sym_base,
+    const int *__restrict__ sym_pref, Src src, const int *__restrict__ out_row, float *__restrict__ out, int n_out,
+    float *__restrict__ pool, uint32_t sym_waves, int64_t pull_limit)
+{
+    struct Tiles {
+        float4 tile[2 * kWave];
+        int tix[kWave];
+        SymRed<256> red;
+    };
+    __shared__ union {
+        Tiles t;
+        float4 stage[kStageForce + kWave];
+    } lds;
+    const bool um = hdr[kHdrMassInfo] == 0;
+    if (blockIdx.x < sym_waves) {
+        if (um)
+            force_sym_items<Acc, kSoft, true, 256>(acc, sym_items, hdr, start, nact, sym_base, sym_pref, src, pool,
+                                                   lds.t.tile, lds.t.tix, lds.t.red, pull_limit, blockIdx.x, sym_waves);
+        else
+            force_sym_items<Acc, kSoft, false, 256>(acc, sym_items, hdr, start, nact, sym_base, sym_pref, src, pool,
+                                                    lds.t.tile, lds.t.tix, lds.t.red, pull_limit, blockIdx.x,
+                                                    sym_waves);
+    } else {
+        const uint32_t wave = blockIdx.x - sym_waves, waves = gridDim.x - sym_waves;
+        if (um)
+            force_items<Acc, kSoft, true>(acc, items, hdr, start, nact, src, out_row, out, n_out, lds.stage,
+                                          pull_limit, wave, waves);
+        else
+            force_items<Acc, kSoft, false>(acc, items, hdr, start, nact, src, out_row, out, n_out, lds.stage,
+                                           pull_limit, wave, waves);
+    }
+}
+
+template <class Acc, bool kSoft>
+__global__ __launch_bounds__(64, 1) void k_vjp_both(
+    Acc acc, const int4 *__restrict__ items, const int4 *__restrict__ sym_items, uint32_t *hdr,
+    const int *__restrict__ start, const int *__restrict__ nact, const int *__restrict__ sym_base,
+    const int *__restrict__ sym_pref, Src src, const float *__restrict__ gx, const float *__restrict__ gy,
+    const float *__restrict__ gz, const int *__restrict__ perm, float *__restrict__ out, int n_out,
+    float *__restrict__ pool, uint32_t sym_waves, int64_t pull_limit)
+{
+    struct Tiles {
+        float4 tile_p[2 * kWave], tile_g[2 * kWave];
+        int tix[kWave];
+        SymRed<256> red;
+    };
+    struct Stage {
+        float4 p[kStageVjp + kWave], g[kStageVjp + kWave];
+    };
+    __shared__ union {
+        Tiles t;
+        Stage s;
+    } lds;
+    const bool um = hdr[kHdrMassInfo] == 0;
+    if (blockIdx.x < sym_waves) {
+        if (um)
+            vjp_sym_items<Acc, kSoft, true, 256>(acc, sym_items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz,
+                                                 pool, lds.t.tile_p, lds.t.tile_g, lds.t.tix, lds.t.red, pull_limit,
+                                                 blockIdx.x, sym_waves);
+        else
+            vjp_sym_items<Acc, kSoft, false, 256>(acc, sym_items, hdr, start, nact, sym_base, sym_pref, src, gx, gy, gz,
+                                                  pool, lds.t.tile_p, lds.t.tile_g, lds.t.tix, lds.t.red, pull_limit,
+                                                  blockIdx.x, sym_waves);
+    } else {
+        const uint32_t wave = blockIdx.x - sym_waves, waves = gridDim.x - sym_waves;
+        if (um)
+            vjp_items<Acc, kSoft, true>(acc, items, hdr, start, nact, src, gx, gy, gz, perm, out, n_out, lds.s.p,
+                                        lds.s.g, pull_limit, wave, waves);
+        else
+            vjp_items<Acc, kSoft, false>(acc, items, hdr, start, nact, src, gx, gy, gz, perm, out, n_out, lds.s.p,
+                                         lds.s.g, pull_limit, wave, waves);
+    }
 }
 
 // Adds up the partial slots of every particle, in a fixed order.  A dense
@@ -2762,14 +2851,17 @@ bool sym_possible(const DevArgs &a)
 
 // Work lists of a pass: with `sym`, the symmetric tiles' shape (or the
 // decision to leave them off), then every cell's items and partial slots.
+// cleared: the header's counters, decisions and queues (everything after the
+// flags, tag and mass words) are zero already.
 template <bool kActiveOnly>
-hipError_t build_lists(const DevArgs &a, int two, bool sym)
+hipError_t build_lists(const DevArgs &a, int two, bool sym, bool cleared)
 {
     const Layout &L = *a.L;
     uint32_t *hdr = at<uint32_t>(a, L.hdr);
-    // counters, decisions and queues (everything after the flags, tag and mass words)
-    hipError_t e = fill_u32(hdr + kHdrBucketCount, kHdrWords - kHdrBucketCount, 0, a.st);
-    if (e != hipSuccess) return e;
+    if (!cleared) {
+        const hipError_t e = fill_u32(hdr + kHdrLists, kHdrWords - kHdrLists, 0, a.st);
+        if (e != hipSuccess) return e;
+    }
     return with_acc(a, [&](auto acc) -> hipError_t {
         using A = decltype(acc);
         if (sym) {
@@ -2961,27 +3053,50 @@ void launch_force_sym(const DevArgs &a, Acc acc)
     }
 }
 
-template <class Acc, bool kSoft, int kW, int kOcc>
-void launch_vjp_sym_v(const DevArgs &a, Acc acc, unsigned grid)
+// Windows of 512; those of 256 go with the one-sided items (vjp_both).
+template <class Acc, bool kSoft>
+void launch_vjp_sym(const DevArgs &a, Acc acc)
 {
     const Layout &L = *a.L;
-    k_vjp_sym<Acc, kSoft, kW, kOcc><<<grid, kWave, 0, a.st>>>(
+    k_vjp_sym<Acc, kSoft, 512><<<(unsigned)sym_waves(a), kWave, 0, a.st>>>(
         acc, at<int4>(a, L.sym_items), at<uint32_t>(a, L.hdr), at<int>(a, L.start), at<int>(a, L.nact),
         at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<float>(a, L.gx), at<float>(a, L.gy),
         at<float>(a, L.gz), at<float>(a, L.sym_pool), a.pull_limit);
 }
 
+// One launch for both kinds of items (windows of 256).  It pays where either
+// kind alone leaves the chip to a few last items: clustered steps of 50,000 /
+// 100,000 (autograd) / 200,000 / 400,000 particles 0.300 -> 0.232, 0.384 ->
+// 0.317, 0.805 -> 0.746, 1.39 -> 1.28 ms.  The adjoint takes it at every size
+// (2.1 million with large halos 12.0 -> 11.25 ms, node share 49.7 -> 48.9,
+// uniform 2 million 0.92 -> 0.935); in the forward the one-sided items lose two
+// of their seven waves per SIMD to the tiles' registers (uniform 2 million 0.66
+// -> 0.73 ms), which from some 300,000 particles on costs more than the tails.
+constexpr int64_t kBothForce = int64_t(1) << 18;
+bool force_both(const DevArgs &a) { return a.sym_window == 256 && a.L->N <= kBothForce; }
+bool vjp_both(const DevArgs &a) { return a.sym_window == 256; }
+
 template <class Acc, bool kSoft>
-void launch_vjp_sym(const DevArgs &a, Acc acc)
+void launch_force_both(const DevArgs &a, Acc acc, float *acc_out)
 {
-    const unsigned grid = (unsigned)sym_waves(a);
-    if (a.sym_window >= 512) {
-        if (a.sym_occupancy >= 5) launch_vjp_sym_v<Acc, kSoft, 512, 5>(a, acc, grid);
-        else launch_vjp_sym_v<Acc, kSoft, 512, 0>(a, acc, grid);
-    } else {
-        if (a.sym_occupancy >= 5) launch_vjp_sym_v<Acc, kSoft, 256, 5>(a, acc, grid);
-        else launch_vjp_sym_v<Acc, kSoft, 256, 0>(a, acc, grid);
-    }
+    const Layout &L = *a.L;
+    const unsigned sw = (unsigned)sym_waves(a);
+    k_force_both<Acc, kSoft><<<sw + persistent_grid(a), kWave, 0, a.st>>>(
+        acc, at<int4>(a, L.items), at<int4>(a, L.sym_items), at<uint32_t>(a, L.hdr), at<int>(a, L.start),
+        at<int>(a, L.nact), at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<int>(a, L.out_row), acc_out,
+        a.n_rows, at<float>(a, L.sym_pool), sw, a.pull_limit);
+}
+
+template <class Acc, bool kSoft>
+void launch_vjp_both(const DevArgs &a, Acc acc, float *grad)
+{
+    const Layout &L = *a.L;
+    const unsigned sw = (unsigned)sym_waves(a);
+    k_vjp_both<Acc, kSoft><<<sw + persistent_grid(a), kWave, 0, a.st>>>(
+        acc, at<int4>(a, L.items), at<int4>(a, L.sym_items), at<uint32_t>(a, L.hdr), at<int>(a, L.start),
+        at<int>(a, L.nact), at<int>(a, L.sym_base), at<int>(a, L.sym_pref), src_of(a), at<float>(a, L.gx),
+        at<float>(a, L.gy), at<float>(a, L.gz), at<int>(a, L.perm()), grad, (int)L.N, at<float>(a, L.sym_pool), sw,
+        a.pull_limit);
 }
 
 // Adds the symmetric partial sums to the rows the one-sided kernel wrote.
@@ -2999,14 +3114,17 @@ hipError_t sym_gather(const DevArgs &a, const int *rows, float *out, int n_out, 
 hipError_t dev_force(const DevArgs &a, float *acc_out)
 {
     const bool sym = sym_possible(a);
-    const hipError_t e = build_lists<true>(a, a.targets_per_lane >= 2 ? 1 : 0, sym);
+    const hipError_t e = build_lists<true>(a, a.targets_per_lane >= 2 ? 1 : 0, sym, a.just_binned);
     if (e != hipSuccess) return e;
     const bool soft = all_softened(a);
     return with_acc(a, [&](auto acc) -> hipError_t {
         using A = decltype(acc);
         void *tok = nullptr;
         timing_begin("force", a.st, &tok);
-        if (soft) {
+        if (sym && force_both(a)) {
+            if (soft) launch_force_both<A, true>(a, acc, acc_out);
+            else launch_force_both<A, false>(a, acc, acc_out);
+        } else if (soft) {
             if (a.occupancy >= 8) launch_force<A, true, 8>(a, acc, acc_out);
             else if (a.occupancy >= 6) launch_force<A, true, 6>(a, acc, acc_out);
             else launch_force<A, true, 0>(a, acc, acc_out);
@@ -3018,8 +3136,10 @@ hipError_t dev_force(const DevArgs &a, float *acc_out)
         hipError_t le = hipGetLastError();
         if (le == hipSuccess && sym) {
             // dense pairs once each; the device skips both when the tiles are off
-            if (soft) launch_force_sym<A, true>(a, acc);
-            else launch_force_sym<A, false>(a, acc);
+            if (!force_both(a)) {
+                if (soft) launch_force_sym<A, true>(a, acc);
+                else launch_force_sym<A, false>(a, acc);
+            }
             if ((le = hipGetLastError()) == hipSuccess)
                 le = sym_gather(a, at<int>(a, a.L->out_row), acc_out, a.n_rows, 1.0f);
         }
@@ -3033,18 +3153,21 @@ hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad)
     const Layout &L = *a.L;
     k_gather_g<<<blocks_for(L.N, 256), 256, 0, a.st>>>((int)L.N, a.n_rows, at<int>(a, L.out_row), g,
                                                       at<float>(a, L.gx), at<float>(a, L.gy),
-                                                      at<float>(a, L.gz));
+                                                      at<float>(a, L.gz), at<uint32_t>(a, L.hdr));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const bool sym = sym_possible(a);
-    if ((e = build_lists<false>(a, a.targets_per_lane >= 2 ? 1 : 0, sym)) != hipSuccess) return e;
+    if ((e = build_lists<false>(a, a.targets_per_lane >= 2 ? 1 : 0, sym, true)) != hipSuccess) return e;
     const bool soft = all_softened(a);
     return with_acc(a, [&](auto acc) -> hipError_t {
         using A = decltype(acc);
         void *tok = nullptr;
         timing_begin("vjp", a.st, &tok);
         // the adjoint kernel spills at 8 waves per SIMD: 6 is its tightest hint
-        if (soft) {
+        if (sym && vjp_both(a)) {
+            if (soft) launch_vjp_both<A, true>(a, acc, grad);
+            else launch_vjp_both<A, false>(a, acc, grad);
+        } else if (soft) {
             if (a.occupancy >= 6) launch_vjp<A, true, 6>(a, acc, grad);
             else launch_vjp<A, true, 0>(a, acc, grad);
         } else {
@@ -3053,8 +3176,10 @@ hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad)
         }
         hipError_t le = hipGetLastError();
         if (le == hipSuccess && sym) {
-            if (soft) launch_vjp_sym<A, true>(a, acc);
-            else launch_vjp_sym<A, false>(a, acc);
+            if (!vjp_both(a)) {
+                if (soft) launch_vjp_sym<A, true>(a, acc);
+                else launch_vjp_sym<A, false>(a, acc);
+            }
             if ((le = hipGetLastError()) == hipSuccess)
                 le = sym_gather(a, at<int>(a, a.L->perm()), grad, (int)a.L->N, -3.0f);
         }
@@ -3073,7 +3198,7 @@ hipError_t dev_count_pairs(const DevArgs &a, bool adjoint, int64_t *pairs)
     const Layout &L = *a.L;
     // every ordered pair from its target's end: no symmetric tiles here (the
     // pair counter is zeroed with the lists)
-    hipError_t e = adjoint ? build_lists<false>(a, 0, false) : build_lists<true>(a, 0, false);
+    hipError_t e = adjoint ? build_lists<false>(a, 0, false, false) : build_lists<true>(a, 0, false, false);
     if (e != hipSuccess) return e;
     e = with_acc(a, [&](auto acc) -> hipError_t {
         k_count<<<persistent_grid(a), kWave, 0, a.st>>>(acc, at<int4>(a, L.items),
