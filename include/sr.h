@@ -215,7 +215,7 @@ sr_status sr_force_vjp(const float *pos, const float *mass, int64_t n, int64_t n
  * [n] (device, read only), acc [n_active][3] (device, overwritten).
  * Returns SR_E_UNSUPPORTED, before touching the device, when the problem
  * needs a larger workspace than that (sr_workspace_bytes gives the need:
- * about 80 B per particle plus 12 B per cell); SR_E_DEVICE if the array's
+ * some 270 B per particle plus 180 B per cell at least); SR_E_DEVICE if the array's
  * address cannot be looked up; other errors as sr_force.  Never calls
  * hipMalloc or hipFree.  Every call on one GPU shares that GPU's array and
  * leaves its contents there (each call re-initialises what it reads), so
@@ -445,7 +445,8 @@ sr_status sr_power_spectrum(sr_pk_plan *plan, const float *pos, const float *mas
  *   targets_per_lane  1 or 2: with 2, a wave holds two targets per lane in cells
  *                     with more than 64 targets (0 keeps the current value);
  *   occupancy         register-allocation variant of the pair kernels: 0 (none),
- *                     6 or 8 waves per SIMD (-1 keeps the current value).
+ *                     6 or 8 waves per SIMD (-1 keeps the current value); the
+ *                     kernels that take both kinds of items have none.
  * None of them changes results: every target sums its sources in the same
  * order.  sr_launch_config sets the forward and adjoint kernels alike and
  * writes the forward kernel's values in effect to cur (host, nullable,
@@ -471,8 +472,9 @@ sr_status sr_launch_config_kernel(const char *kernel /*host*/, int waves_per_cu,
  * need fewer partial slots but spread worse; with a balance ratio above 0
  * (sr_tile_balance) the device cuts items down to a sixteenth of these blocks
  * where there is little work.  The partial slots (12 bytes each)
- * fill the tail of the workspace: sr_workspace_bytes reserves about 15 per
- * particle (up to 47 from 2^19 particles on, at most 805 MB more), and a
+ * fill the tail of the workspace: sr_workspace_bytes reserves 16 to 48 per
+ * particle (more than 16 as far as SR_STATIC_WORKSPACE_BYTES hold them, and
+ * from 2^19 particles on up to 805 MB), and a
  * larger workspace passed to sr_force / sr_force_vjp lends
  * its whole tail to them.  A problem that needs more (very large cells) runs
  * without symmetric tiles.  Results differ from the one-sided sums only in rounding

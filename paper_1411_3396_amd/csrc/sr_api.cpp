@@ -132,15 +132,19 @@ void sym_tail(Layout &L, size_t ws_bytes)
     L.sym_pool = L.sym_items + align256((size_t)L.sym_item_cap * 16);
 }
 
-// Partial slots of a layout: 16 per particle, and from 2^19 particles on up to
-// 32 more (at most 2^26, 805 MB) for boxes with a few very large halos: the
-// 2.1 million particle box whose halos reach 55,000 particles a cell needs 31
-// at items of 16 blocks and two windows.  Smaller problems keep to what the
-// fixed workspace of sr_force_static was sized for.
-int64_t sym_slots(int64_t N)
+// Partial slots of a layout whose other buffers end at byte `at`: 16 per
+// particle, and up to 32 more for boxes with a few very large halos (the 2.1
+// million particle box whose halos reach 55,000 particles a cell needs 31 at
+// items of 16 blocks and two windows; a box of 30,000 particles, half of them
+// in halos, 18 to 42).  From 2^19 particles on at most 2^26 more (805 MB);
+// below, as many as the fixed workspace of sr_force_static still holds.
+int64_t sym_slots(int64_t N, size_t at)
 {
-    const int64_t more = N >= (int64_t(1) << 19) ? std::min<int64_t>(32 * N, int64_t(1) << 26) : 0;
-    return kSymSlotsPerParticle * N + more;
+    const int64_t least = kSymSlotsPerParticle * N, most = 3 * least;
+    if (N >= (int64_t(1) << 19)) return std::min(most, least + (int64_t(1) << 26));
+    const size_t fixed = SR_STATIC_WORKSPACE_BYTES;
+    const int64_t fit = fixed > at + 1024 ? (int64_t)((fixed - at - 1024) / 784 * 64) : 0;
+    return std::max(least, std::min(most, fit));
 }
 
 Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_passive, int code_bits)
@@ -203,7 +207,7 @@ Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_pas
     L.sym_info = take((size_t)NC * 4);
     // the tail: symmetric items and the pool, sized for the default number of
     // slots per particle; a larger workspace lends the tail more (sym_tail)
-    const int64_t cap = std::min<int64_t>(sym_slots(N), kSymMaxSlots);
+    const int64_t cap = std::min<int64_t>(sym_slots(N, o), kSymMaxSlots);
     L.sym_items = o;
     L.total = o + sym_tail_bytes(cap);
     sym_tail(L, L.total);
