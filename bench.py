@@ -11,12 +11,12 @@ the forward pass + useful pairs of the adjoint pass) / step time.  A useful
 pair is an ordered (target, source) pair with 0 < r < r_s; the forward's have
 an active target, the adjoint's at least one active end (a pair of two ghosts
 adds exactly nothing to the gradient and is not evaluated).  A pass (forward
-or adjoint) is three kernels: the one-sided items, the symmetric tiles of the
-dense cells and the gather of their partial sums, timed together with HIP
-events on the launch stream.  The forward pass's own rate (useful forward
-pairs / forward pass time) is forward_pairs_per_s.  `roofline` is the
-dominant pass's (the adjoint's, the longest), with both passes under
-roofline_forward and roofline_adjoint.
+or adjoint) is the one-sided items, the symmetric tiles of the dense cells (in
+the adjoint and in small forwards both in one kernel) and the gather of the
+tiles' partial sums, timed together with HIP events on the launch stream.  The
+forward pass's own rate (useful forward pairs / forward pass time) is
+forward_pairs_per_s.  `roofline` is the dominant pass's (the adjoint's, the
+longest), with both passes under roofline_forward and roofline_adjoint.
 """
 from __future__ import annotations
 
@@ -37,10 +37,10 @@ PEAK_FP32_VECTOR = 157.3  # TFLOP/s, MI355X (packed), 256 CUs x 2.4 GHz x 256 fl
 PEAK_FP32_NONPACKED = 78.6  # TFLOP/s, one float32 FMA per lane per clock
 FLOP_PER_PAIR = {"force": 30, "vjp": 61}
 # the kernels of one pass: one-sided items (sparse cells, remainders and the
-# non-dense sources of dense blocks), symmetric tiles of the dense cells, and
-# the gather of the symmetric partial sums
+# non-dense sources of dense blocks) and symmetric tiles of the dense cells, in
+# one launch in the adjoint, and the gather of the symmetric partial sums
 PASS_KERNELS = {"force": ["k_force", "k_force_sym", "k_sym_gather"],
-                "vjp": ["k_vjp", "k_vjp_sym", "k_sym_gather"]}
+                "vjp": ["k_vjp_both", "k_sym_gather"]}
 PASS_NAME = {"force": "forward", "vjp": "adjoint"}
 
 
