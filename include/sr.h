@@ -487,6 +487,8 @@ sr_status sr_tile_config(const char *kernel /*host*/, int blocks_per_item, int w
  * with fewer than 64 targets: 8, 16, 32 or 64 (-1 keeps the value; initial
  * 16, or SR_SPARSE_GROUP).  Smaller groups have tighter boxes and stage their
  * sources more often; the choice changes only the order of float32 sums.
+ * With 16, sr_force and sr_force_vjp of at most 32,768 targets (the adjoint's
+ * are all particles) take 8: they leave waves idle otherwise.
  * Batch plans tune their own.  cur (nullable) receives the value in effect. */
 sr_status sr_sparse_group(int group, int *cur /*host out*/);
 

@@ -340,3 +340,29 @@ def test_sparse_group_sizes_match_oracle(group):
     assert e <= VJP_TOL, e
     assert oracle.rms_rel(a, a16) <= 2e-6
     assert oracle.rms_rel(gr, g16) <= 2e-5
+
+
+@pytest.mark.parametrize("n", [1, 700, 32767, 32768, 32769])
+def test_default_sparse_group_at_the_edge_of_its_rule(n):
+    # up to 32,768 targets the default of 16 targets per sparse item is 8; the
+    # value in effect stays 16, and the sums are those of a configured 8, bit
+    # for bit, and of 16 above
+    w = synth.uniform_box(n, 22.0, 71)
+    g = synth.cotangent(w.n_active, 13)
+    announce(f"sparse group rule n={n}")
+    saved = sr.sparse_group()
+    try:
+        sr.sparse_group(16)
+        a, gr = gpu_force(w), gpu_vjp(w, g)
+        assert sr.sparse_group() == 16
+        sr.sparse_group(8)
+        a8, g8 = gpu_force(w), gpu_vjp(w, g)
+    finally:
+        sr.sparse_group(saved)
+    assert_force_close(a, oracle_force(w), what=f"n={n}")
+    e = oracle.rms_rel(gr, oracle.vjp(w.pos, w.mass, w.n_active, w.problem, g))
+    assert e <= VJP_TOL, e
+    if n <= 32768:
+        assert np.array_equal(a, a8) and np.array_equal(gr, g8)
+    assert oracle.rms_rel(a, a8) <= 2e-6
+    assert oracle.rms_rel(gr, g8) <= 2e-5
