@@ -497,7 +497,8 @@ sr_status sr_sparse_group(int group, int *cur /*host out*/);
  * spread over the persistent grid's waves is at least 5 min_ratio times the
  * longest item, and smaller otherwise, so that a few long items cannot leave
  * most waves idle; the tiles are off only when the smallest items' work does
- * not even give four waves per compute unit min_ratio times the longest one.
+ * not even give four waves per compute unit min_ratio times the longest one (a
+ * sixteenth of that for items of at most 1,024 tile steps).
  * The decision is taken on the device after binning, like the pool check.
  * min_ratio >= 0 (0: always the configured items, whenever their partial
  * slots fit; -1 keeps the value); initial value 1, or SR_SYM_BALANCE.  Batch plans do not

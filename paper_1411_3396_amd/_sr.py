@@ -683,7 +683,8 @@ def tile_balance(min_ratio: float = -1.0) -> float:
     """Set and return the balance rule of the symmetric tiles: their items are cut smaller while
     the work per wave of the persistent grid is below 5 min_ratio longest items, and the tiles are
     off when the smallest items' work gives four waves per compute unit less than min_ratio longest
-    ones (0: the configured items whenever the partial slots fit; -1 keeps the value)."""
+    ones, a sixteenth of it for items of at most 1,024 tile steps (0: the configured items whenever
+    the partial slots fit; -1 keeps the value)."""
     cur = C.c_double()
     _check(lib().sr_tile_balance(float(min_ratio), C.byref(cur)), "sr_tile_balance")
     return float(cur.value)

@@ -214,3 +214,23 @@ def test_item_shape_follows_the_work(n, side, halo_frac, masses):
     torch.cuda.synchronize()
     hdr = ws[4 * 518:4 * 524].view(torch.int32).tolist()
     assert hdr[0] == 1 and 1 <= hdr[4] < 16 and 1 <= hdr[5] <= 2
+
+
+@pytest.mark.parametrize("n,side,halo_frac,on", [(4095, 12.0, 0.5, 1), (5000, 14.0, 0.6, 1), (12000, 20.0, 0.5, 1),
+                                                 (5000, 40.0, 0.02, 0)])
+def test_short_items_of_little_work(n, side, halo_frac, on):
+    # a few thousand particles with much of their matter in a few cells: a
+    # sixteenth of a longest item's work per wave (of four a compute unit, or
+    # fewer when the problem's grid is smaller) is enough for items of at most
+    # 1,024 tile steps; with no dense cell the tiles stay off.  Oracle parity
+    # and rounding-order agreement with the one-sided sums either way
+    w = synth.clustered_box(n, side, 6, 31, halo_frac=halo_frac, mass_range=(1e3, 2e3))
+    w.mass = np.random.default_rng(8).uniform(0.5, 2.0, w.n).astype(np.float32)
+    g = synth.cotangent(w.n_active, 9)
+    announce(f"short items n={w.n}")
+    a, gr, ok_f, ok_v = run(w, g, balance=1.0)
+    assert ok_f == on and ok_v == on
+    assert_force_close(a, oracle_force(w), what="short items")
+    assert oracle.rms_rel(gr, oracle.vjp(w.pos, w.mass, w.n_active, w.problem, g)) <= VJP_TOL
+    a0, g0, _, _ = run(w, g, (0, -1))
+    assert oracle.rms_rel(a, a0) <= 2e-6 and oracle.rms_rel(gr, g0) <= 2e-5
