@@ -619,6 +619,12 @@ sr_status sr_centres_plan_create(int32_t n_halos, const int64_t *offsets, sr_cen
         if (offsets[h + 1] < offsets[h]) return SR_E_ARG;
     const int64_t n = offsets[n_halos];
     if (n > (int64_t(1) << 31) - 1) return SR_E_UNSUPPORTED;
+    // an item's word holds its slot among the partial minima in 26 bits: every halo
+    // counts as its one-sided items, at least as many as a pair-once halo has chunks
+    int64_t most = 0;
+    for (int h = 0; h < n_halos; ++h)
+        most += (offsets[h + 1] - offsets[h] + 2 * kTargetsPerWave - 1) / (2 * kTargetsPerWave);
+    if (most > (int64_t(1) << 26)) return SR_E_UNSUPPORTED;
     // items of each halo: up to 128 targets (two per lane), a last group of at
     // most 64 one per lane, halos under 64 with 2^lk lanes per target
     struct Item {
@@ -652,7 +658,6 @@ sr_status sr_centres_plan_create(int32_t n_halos, const int64_t *offsets, sr_cen
         }
         hbase[h + 1] = hbase[h] + chunk;
     }
-    if (items.size() > (size_t(1) << 26)) return SR_E_UNSUPPORTED;
     // slot = position of the item inside its halo's range, fixed before sorting
     for (size_t k = 0, h = 0, c = 0; k < items.size(); ++k) {
         if ((int)h != items[k].h) {

@@ -48,3 +48,14 @@ def test_workspace_grows_with_items():
     a = _create([0, 100])[2]
     b = _create(np.arange(0, 100001, 100))[2]
     assert 0 < a < b
+
+
+def test_item_slots_fit_their_bits():
+    # 2^26 halos, all but one of a single particle: the last one's chunks come on top, and an
+    # item's slot among the partial minima no longer fits 26 bits
+    off = np.arange((1 << 26) + 1, dtype=np.int64)
+    off[-1] += 299
+    code, plan, _ = _create(off)
+    if code == 0:
+        _sr.lib().sr_centres_plan_destroy(plan)
+    assert code == 5
