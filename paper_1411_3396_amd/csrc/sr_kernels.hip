@@ -1561,6 +1561,9 @@ __device__ __forceinline__ uint64_t load_agent(const uint32_t *p)
     return __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Orders memory operations for the compiler alone; no instruction.
+__device__ __forceinline__ void compiler_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "singlethread"); }
+
 // Only cells with dense particles look at their stencil.  `few`: the waves the
 // finest shape has to keep busy.  At most kListBlocks workgroups stride over
 // the cells: their totals are atomic adds to one line, some 8 ns each (one
@@ -1635,11 +1638,16 @@ __global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__
     }
     if (threadIdx.x == 0 && work) atomicAdd((unsigned long long *)&hdr[kHdrSymWork], work);
     // everything the last workgroup reads is added by device-scope atomics, so
-    // waiting for them is enough (a device-scope fence would write the L2 back)
+    // waiting for them is enough (a device-scope fence would write the L2 back);
+    // the fences keep the compiler from moving them past the wait, and the last
+    // workgroup's loads above its count
+    compiler_fence();
     __builtin_amdgcn_s_waitcnt(0);
+    compiler_fence();
     __syncthreads();
     if (threadIdx.x == 0) rank = atomicAdd(&hdr[kHdrSymDone], 1u);
     __syncthreads();
+    compiler_fence();
     if (rank != gridDim.x - 1) return;
     // the last workgroup: all totals read at once
     if (threadIdx.x < kSymShapes) {
