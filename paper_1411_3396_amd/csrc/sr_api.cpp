@@ -132,19 +132,20 @@ void sym_tail(Layout &L, size_t ws_bytes)
     L.sym_pool = L.sym_items + align256((size_t)L.sym_item_cap * 16);
 }
 
-// Partial slots of a layout whose other buffers end at byte `at`: 16 per
+// Bytes of a layout whose other buffers end at byte `at`: 16 partial slots per
 // particle, and up to 32 more for boxes with a few very large halos (the 2.1
 // million particle box whose halos reach 55,000 particles a cell needs 31 at
 // items of 16 blocks and two windows; a box of 30,000 particles, half of them
 // in halos, 18 to 42).  From 2^19 particles on at most 2^26 more (805 MB);
-// below, as many as the fixed workspace of sr_force_static still holds.
-int64_t sym_slots(int64_t N, size_t at)
+// below, as many as the fixed workspace of sr_force_static still holds.  Never
+// falls as N grows, since each of the three terms does not, so a workspace
+// sized for the most particles serves every smaller call too.
+size_t layout_bytes(int64_t N, size_t at)
 {
     const int64_t least = kSymSlotsPerParticle * N, most = 3 * least;
-    if (N >= (int64_t(1) << 19)) return std::min(most, least + (int64_t(1) << 26));
-    const size_t fixed = SR_STATIC_WORKSPACE_BYTES;
-    const int64_t fit = fixed > at + 1024 ? (int64_t)((fixed - at - 1024) / 784 * 64) : 0;
-    return std::max(least, std::min(most, fit));
+    const auto with = [&](int64_t slots) { return at + sym_tail_bytes(std::min(slots, kSymMaxSlots)); };
+    if (N >= (int64_t(1) << 19)) return with(std::min(most, least + (int64_t(1) << 26)));
+    return std::max(with(least), std::min(with(most), (size_t)SR_STATIC_WORKSPACE_BYTES));
 }
 
 Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_passive, int code_bits)
@@ -207,9 +208,8 @@ Layout make_layout(int64_t N, int64_t NC, int B, int64_t mom_tiles, bool any_pas
     L.sym_info = take((size_t)NC * 4);
     // the tail: symmetric items and the pool, sized for the default number of
     // slots per particle; a larger workspace lends the tail more (sym_tail)
-    const int64_t cap = std::min<int64_t>(sym_slots(N, o), kSymMaxSlots);
     L.sym_items = o;
-    L.total = o + sym_tail_bytes(cap);
+    L.total = layout_bytes(N, o);
     sym_tail(L, L.total);
     return L;
 }

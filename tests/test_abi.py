@@ -71,6 +71,18 @@ def test_workspace_bytes_grows_with_n():
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("length", [12.0, 40.0, 100.0])
+def test_workspace_need_never_falls_as_n_grows(length):
+    # a workspace sized for the most particles a program meets has to serve every smaller call:
+    # through the sizes whose slots are bounded by the fixed workspace (some 91,000 to 250,000
+    # particles), and across the step at 2^19
+    p = prob(length)
+    need = [_sr.workspace_bytes(n, p) for n in
+            [*range(500, 420000, 500), (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 10 ** 6]]
+    assert all(b % 256 == 0 for b in need)
+    assert need == sorted(need)
+
+
 def _force(n=100, n_active=100, p=None, ws=FAKE, ws_bytes=None, flags=0, pos=FAKE, mass=FAKE,
            acc=FAKE):
     p = p if p is not None else prob()
