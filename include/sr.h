@@ -269,7 +269,9 @@ sr_status sr_batch_plan_create(int32_t B, const int64_t *offsets /*host [B+1]*/,
 
 /* Run a batch: acc [sum n_active][3]; momentum (nullable) [B][3] float64 =
  * sum over active rows of mass * acc per subvolume.  flags:
- * SR_BATCH_PER_SUBVOLUME (one sr_force per subvolume, the reference mode),
+ * SR_BATCH_PER_SUBVOLUME (one launch sequence per subvolume, the reference
+ * mode; it bins the whole batch once more before them, to run the symmetric
+ * tiles in all subvolumes or none, as the batched modes do),
  * SR_BATCH_EAGER (batched kernels without a graph), 0 (graph replay; with
  * SR_BATCH_RECAPTURE, capture again for new pointers).  The first run, in
  * any mode, tunes the launch parameters, the symmetric tiles and the targets

@@ -362,6 +362,7 @@ sr_status device_args(DevArgs &a, void *ws, const Layout *L, const SegParams *se
     a.sparse_group = g_sparse_group.load();
     a.pull_limit = pull_limit();
     a.just_binned = false;
+    a.sym_gate = nullptr;
     return SR_OK;
 }
 
@@ -439,6 +440,7 @@ struct sr_batch_plan {
     SegParams summary{};                // softened = all subvolumes softened
     Layout L;
     size_t ws_bytes = 0;
+    size_t gate = 0;                    // per-subvolume mode: byte of the word that lets the symmetric tiles run
     int64_t total_active = 0;
     SegParams *pinned = nullptr;        // upload source of the segment table
     hipStream_t cap = nullptr;          // capture stream
@@ -459,13 +461,11 @@ struct sr_batch_plan {
 
 namespace {
 
-sr_status run_batched(sr_batch_plan *P, const float *pos, const float *mass, void *ws, float *acc,
-                      double *mom, hipStream_t st)
+// Launch arguments of a batched run, and the plan's tuned choices for either mode.
+sr_status batch_args(DevArgs &a, const sr_batch_plan *P, void *ws, const Layout *L, const SegParams *seg_host,
+                     const SegParams *seg_dev, hipStream_t st, int64_t n_rows)
 {
-    DevArgs a;
-    sr_status s = device_args(a, ws, &P->L, &P->summary, reinterpret_cast<SegParams *>(
-                                  static_cast<char *>(ws) + P->L.seg), st, P->waves_per_cu,
-                                  P->total_active);
+    const sr_status s = device_args(a, ws, L, seg_host, seg_dev, st, P->waves_per_cu, n_rows);
     if (s != SR_OK) return s;
     a.targets_per_lane = P->targets_per_lane;
     a.occupancy = P->occupancy;
@@ -478,34 +478,64 @@ sr_status run_batched(sr_batch_plan *P, const float *pos, const float *mass, voi
     // one window per item: the tuner's tile choices were timed that way, and
     // a plan's many small problems gain little from fewer target slots
     a.sym_rounds = 1;
-    hipError_t e = hipMemcpyAsync(static_cast<char *>(ws) + P->L.seg, P->pinned,
-                                  sizeof(SegParams) * P->B, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return SR_E_DEVICE;
-    if ((e = dev_bin(a, pos, mass)) != hipSuccess) return SR_E_DEVICE;
-    a.just_binned = true;
-    if (P->total_active > 0 && (e = dev_force(a, acc)) != hipSuccess) return SR_E_DEVICE;
-    if (mom && (e = dev_momentum(a, acc, mass, mom)) != hipSuccess) return SR_E_DEVICE;
     return SR_OK;
 }
 
+// Bins the batch as one and leaves `a` ready for its pair kernels.
+sr_status bin_batched(sr_batch_plan *P, DevArgs &a, const float *pos, const float *mass, void *ws, hipStream_t st)
+{
+    const sr_status s = batch_args(a, P, ws, &P->L, &P->summary,
+                                   reinterpret_cast<SegParams *>(static_cast<char *>(ws) + P->L.seg), st,
+                                   P->total_active);
+    if (s != SR_OK) return s;
+    if (hipMemcpyAsync(static_cast<char *>(ws) + P->L.seg, P->pinned, sizeof(SegParams) * P->B,
+                       hipMemcpyHostToDevice, st) != hipSuccess)
+        return SR_E_DEVICE;
+    if (dev_bin(a, pos, mass) != hipSuccess) return SR_E_DEVICE;
+    a.just_binned = true;
+    return SR_OK;
+}
+
+sr_status run_batched(sr_batch_plan *P, const float *pos, const float *mass, void *ws, float *acc,
+                      double *mom, hipStream_t st)
+{
+    DevArgs a;
+    const sr_status s = bin_batched(P, a, pos, mass, ws, st);
+    if (s != SR_OK) return s;
+    if (P->total_active > 0 && dev_force(a, acc) != hipSuccess) return SR_E_DEVICE;
+    if (mom && dev_momentum(a, acc, mass, mom) != hipSuccess) return SR_E_DEVICE;
+    return SR_OK;
+}
+
+// One launch sequence per subvolume.  The symmetric tiles run in all of them or
+// in none, as in a batched run: whether the batch's partial slots fit its pool
+// is found first, on the batch binned as one, and kept beyond the subvolumes'
+// layouts, whose pools hold what the batch's does.  (A batch of one needs no
+// gate: its pool decides.)
 sr_status run_per_subvolume(sr_batch_plan *P, const float *pos, const float *mass, void *ws,
                             float *acc, double *mom, hipStream_t st)
 {
     int64_t out_off = 0;
+    uint32_t *gate = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + P->gate);
+    if (P->B == 1) gate = nullptr;
+    if (gate && P->total_active > 0) {
+        DevArgs a;
+        const sr_status s = batch_args(a, P, ws, &P->L, &P->summary, nullptr, st, P->total_active);
+        if (s != SR_OK) return s;
+        if (a.sym_blocks > 0) {
+            const sr_status s2 = bin_batched(P, a, pos, mass, ws, st);
+            if (s2 != SR_OK) return s2;
+            if (dev_sym_decide(a, gate) != hipSuccess) return SR_E_DEVICE;
+        }
+    }
     for (int b = 0; b < P->B; ++b) {
         Single &S = P->singles[b];
         const int64_t off = P->offsets[b];
         const int64_t n = P->offsets[b + 1] - off;
         DevArgs a;
-        sr_status s = device_args(a, ws, &S.L, &S.seg, nullptr, st, P->waves_per_cu, P->n_active[b]);
+        sr_status s = batch_args(a, P, ws, &S.L, &S.seg, nullptr, st, P->n_active[b]);
         if (s != SR_OK) return s;
-        a.targets_per_lane = P->targets_per_lane;
-        a.occupancy = P->occupancy;
-        if (P->sym_blocks >= 0) a.sym_blocks = P->sym_blocks;
-        if (P->sym_window > 0) a.sym_window = P->sym_window;
-        if (P->sparse_group > 0) a.sparse_group = P->sparse_group;
-        a.sym_balance = 0.0;
-        a.sym_rounds = 1;
+        a.sym_gate = gate;
         if (n > 0) {
             if (dev_bin(a, pos + 3 * off, mass + off) != hipSuccess) return SR_E_DEVICE;
             a.just_binned = true;
@@ -933,7 +963,6 @@ sr_status sr_batch_plan_create(int32_t B, const int64_t *offsets, const int64_t 
     P->segs.resize(B);
     P->singles.resize(B);
     int64_t cell_off = 0, out_off = 0, tile_off = 0;
-    size_t single_max = 0;
     bool soft = true;
     for (int b = 0; b < B; ++b) {
         const int64_t n = offsets[b + 1] - offsets[b];
@@ -942,7 +971,6 @@ sr_status sr_batch_plan_create(int32_t B, const int64_t *offsets, const int64_t 
             delete P;
             return st;
         }
-        single_max = std::max(single_max, P->singles[b].L.total);
         SegParams s = P->singles[b].seg;
         s.cell_off = (int32_t)cell_off;
         s.part_off = (int32_t)offsets[b];
@@ -972,9 +1000,19 @@ sr_status sr_batch_plan_create(int32_t B, const int64_t *offsets, const int64_t 
         return SR_E_UNSUPPORTED;
     }
     P->L = make_layout(offsets[B], cell_off, B, tile_off, any_passive, 3 * depth);
-    // per-subvolume momentum scratch sits at the end of the workspace
+    // in per-subvolume mode a subvolume's layout ends in as many partial slots as
+    // the batch's; behind it lie the word that lets the tiles run and, at the end
+    // of the workspace, the momentum scratch
     const size_t mom_tail = align256((size_t)(3 * mom_tiles_of(offsets[B]) + 3) * 8) + 512;
-    P->ws_bytes = std::max(P->L.total, single_max + mom_tail);
+    size_t single_max = 0;
+    for (Single &S : P->singles) {
+        S.L.total = std::max(S.L.total, S.L.sym_items + sym_tail_bytes(P->L.sym_cap) + 2048);
+        sym_tail(S.L, S.L.total);
+        S.L.sym_cap = std::min(S.L.sym_cap, P->L.sym_cap);
+        single_max = std::max(single_max, align256(S.L.total));
+    }
+    P->gate = single_max;
+    P->ws_bytes = std::max(P->L.total, single_max + 256 + mom_tail);
     if (hipHostMalloc((void **)&P->pinned, sizeof(SegParams) * B, hipHostMallocDefault) != hipSuccess) {
         delete P;
         return SR_E_DEVICE;

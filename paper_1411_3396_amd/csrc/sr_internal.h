@@ -154,11 +154,14 @@ struct DevArgs {
     double sym_balance;    // symmetric tiles: how well their items must spread over the waves (0: one fixed shape)
     int sparse_group;      // most targets per item of a cell (or remainder) with fewer than 64: 8, 16, 32 or 64
     int64_t pull_limit;    // most items one wave of a persistent kernel may pull (test hook)
+    const uint32_t *sym_gate;  // where not null, a device word: the symmetric tiles run only if it is not zero
     bool just_binned;      // dev_bin ran right before on this workspace: the work lists' header words are zero
 };
 
 hipError_t dev_bin(const DevArgs &a, const float *pos, const float *mass);
 hipError_t dev_force(const DevArgs &a, float *acc);
+// Whether a forward pass on these bins runs the symmetric tiles, to *ok (device, outside the layout).
+hipError_t dev_sym_decide(const DevArgs &a, uint32_t *ok);
 hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad);
 hipError_t dev_count_pairs(const DevArgs &a, bool adjoint, int64_t *pairs);
 hipError_t dev_zero(void *p, int64_t words, hipStream_t st);

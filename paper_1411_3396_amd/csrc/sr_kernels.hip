@@ -1567,14 +1567,15 @@ __device__ __forceinline__ void compiler_fence() { __builtin_amdgcn_fence(__ATOM
 // Only cells with dense particles look at their stencil.  `few`: the waves the
 // finest shape has to keep busy.  At most kListBlocks workgroups stride over
 // the cells: their totals are atomic adds to one line, some 8 ns each (one
-// workgroup per 256 cells took 375 us on 1.26 million cells).
+// workgroup per 256 cells took 375 us on 1.26 million cells).  gate (nullable):
+// a word that is zero where the tiles have to stay off.
 constexpr unsigned kListBlocks = 512;
 
 template <class Acc>
 __global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__restrict__ start,
                                                   const int *__restrict__ nact, SymShapes sh, uint32_t *hdr,
                                                   uint32_t magic, unsigned long long cap, int waves, int few,
-                                                  double balance)
+                                                  double balance, const uint32_t *gate)
 {
     __shared__ unsigned long long slots[kSymShapes], work;
     __shared__ uint32_t longest[kSymShapes], rank;
@@ -1661,7 +1662,7 @@ __global__ __launch_bounds__(256) void k_sym_plan(Acc acc, int NC, const int *__
     if (threadIdx.x != 0) return;
     const double w = (double)work;
     int pick = -1;
-    if (w > 0.0) {
+    if (w > 0.0 && (!gate || *gate != 0u)) {
         auto fits = [&](int i) { return slots[i] <= cap; };
         auto len = [&](int i) { return (double)longest[i]; };
         for (int i = 0; i < sh.n && pick < 0; ++i)
@@ -2869,6 +2870,37 @@ bool sym_possible(const DevArgs &a)
     return a.sym_blocks > 0 && n / kWave * std::max(1.0, n / a.sym_window) >= a.sym_balance * sym_few(a);
 }
 
+// The symmetric tiles' shape, or the decision to leave them off, in the header.
+template <class Acc>
+hipError_t plan_tiles(const DevArgs &a, Acc acc)
+{
+    const Layout &L = *a.L;
+    SymShapes sh{};
+    sh.W = a.sym_window;
+    auto add = [&](int k, int r) {
+        k = k < 1 ? 1 : k;
+        if (sh.n > 0 && sh.K[sh.n - 1] == k && sh.R[sh.n - 1] == r) return;
+        sh.K[sh.n] = k;
+        sh.R[sh.n++] = r;
+    };
+    add(a.sym_blocks, a.sym_rounds);
+    if (a.sym_balance > 0.0) {
+        add(a.sym_blocks / 2, a.sym_rounds);
+        add(a.sym_blocks / 4, a.sym_rounds);
+        add(a.sym_blocks / 4, 1);
+        add(a.sym_blocks / 8, 1);
+        add(a.sym_blocks / 16, 1);
+    }
+    for (int i = sh.n; i < kSymShapes; ++i) {
+        sh.K[i] = sh.K[sh.n - 1];
+        sh.R[i] = sh.R[sh.n - 1];
+    }
+    k_sym_plan<<<std::min(blocks_for(L.NC, 256), kListBlocks), 256, 0, a.st>>>(
+        acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), sh, at<uint32_t>(a, L.hdr), L.magic(),
+        (unsigned long long)L.sym_cap, sym_waves(a), sym_few(a), a.sym_balance, a.sym_gate);
+    return hipGetLastError();
+}
+
 // Work lists of a pass: with `sym`, the symmetric tiles' shape (or the
 // decision to leave them off), then every cell's items and partial slots.
 // cleared: the header's counters, decisions and queues (everything after the
@@ -2885,30 +2917,7 @@ hipError_t build_lists(const DevArgs &a, int two, bool sym, bool cleared)
     return with_acc(a, [&](auto acc) -> hipError_t {
         using A = decltype(acc);
         if (sym) {
-            SymShapes sh{};
-            sh.W = a.sym_window;
-            auto add = [&](int k, int r) {
-                k = k < 1 ? 1 : k;
-                if (sh.n > 0 && sh.K[sh.n - 1] == k && sh.R[sh.n - 1] == r) return;
-                sh.K[sh.n] = k;
-                sh.R[sh.n++] = r;
-            };
-            add(a.sym_blocks, a.sym_rounds);
-            if (a.sym_balance > 0.0) {
-                add(a.sym_blocks / 2, a.sym_rounds);
-                add(a.sym_blocks / 4, a.sym_rounds);
-                add(a.sym_blocks / 4, 1);
-                add(a.sym_blocks / 8, 1);
-                add(a.sym_blocks / 16, 1);
-            }
-            for (int i = sh.n; i < kSymShapes; ++i) {
-                sh.K[i] = sh.K[sh.n - 1];
-                sh.R[i] = sh.R[sh.n - 1];
-            }
-            k_sym_plan<<<std::min(blocks_for(L.NC, 256), kListBlocks), 256, 0, a.st>>>(
-                acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), sh, hdr, L.magic(),
-                (unsigned long long)L.sym_cap, sym_waves(a), sym_few(a), a.sym_balance);
-            const hipError_t e2 = hipGetLastError();
+            const hipError_t e2 = plan_tiles(a, acc);
             if (e2 != hipSuccess) return e2;
         }
         k_cells<A, kActiveOnly><<<std::min(blocks_for(L.NC, kCellThreads), 4 * kListBlocks), kCellThreads, 0, a.st>>>(
@@ -3166,6 +3175,23 @@ hipError_t dev_force(const DevArgs &a, float *acc_out)
         timing_end(tok, a.st);
         return le;
     });
+}
+
+__global__ void k_copy_word(const uint32_t *from, uint32_t *to) { *to = *from; }
+
+hipError_t dev_sym_decide(const DevArgs &a, uint32_t *ok)
+{
+    uint32_t *hdr = at<uint32_t>(a, a.L->hdr);
+    if (!a.just_binned) {
+        const hipError_t e = fill_u32(hdr + kHdrLists, kHdrWords - kHdrLists, 0, a.st);
+        if (e != hipSuccess) return e;
+    }
+    if (sym_possible(a)) {
+        const hipError_t e = with_acc(a, [&](auto acc) -> hipError_t { return plan_tiles(a, acc); });
+        if (e != hipSuccess) return e;
+    }
+    k_copy_word<<<1, 1, 0, a.st>>>(hdr + kHdrSymOk, ok);
+    return hipGetLastError();
 }
 
 hipError_t dev_vjp(const DevArgs &a, const float *g, float *grad)

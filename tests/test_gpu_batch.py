@@ -195,3 +195,48 @@ def test_dense_batch_symmetric_tiles_agree_bitwise():
         assert_force_close(out["graph"][row: row + part.n_active], ref, what=f"dense subvolume {k}")
         row += part.n_active
     plan.close()
+
+
+@pytest.mark.parametrize("tile,on,parts", [
+    ((16, 512), 0, lambda: [synth.clustered_box(30000, 18.0, 30, 21 + k, halo_frac=0.9, mass_range=(5e3, 2e4))
+                            for k in range(12)]),
+    ((4, 256), 1, lambda: [synth.clustered_box(150000, 30.0, 30, 5, halo_frac=0.8, mass_range=(1e4, 4e4)),
+                           synth.uniform_box(400000, 110.0, 3)])])
+def test_modes_agree_where_the_slots_fit_one_pool_only(tmp_path, tile, on, parts):
+    # a subvolume's own workspace holds up to 48 partial slots per particle, the batch's
+    # (by its size) 16 to 48: once the batch's 17 per particle do not fit its 16, so
+    # the tiles stay off although every subvolume's would fit its own; once the batch's
+    # fit, although the first subvolume's 28 do not fit what its own size gets.  The
+    # tiles run in all modes or in none, with the same bits
+    parts = parts()
+    pos = np.concatenate([p.pos for p in parts]).astype(np.float32)
+    mass = np.concatenate([p.mass for p in parts]).astype(np.float32)
+    offsets = np.concatenate([[0], np.cumsum([p.n for p in parts])]).astype(np.int64)
+    b = synth.Batch("pools", pos, mass, offsets, np.array([p.n_active for p in parts], np.int64),
+                    [p.problem for p in parts])
+    probe = sr.BatchPlan(b.offsets, b.n_active, b.problems)
+    key = probe.info()["tune_key"]
+    probe.close()
+    cache = tmp_path / "tune.json"
+    cache.write_text('{\n  "%s": {"waves_per_cu": 32, "targets_per_lane": 1, "occupancy": 0, "sym_blocks": %d, '
+                     '"sym_window": %d, "sparse_group": 16, "ms": 1.0}\n}\n' % (key, *tile))
+    plan = sr.BatchPlan(b.offsets, b.n_active, b.problems, tune_cache=str(cache))
+    announce(f"batch pools B={b.size} n={b.pos.shape[0]} tile={tile}")
+    ws = sr.new_workspace(plan.ws_bytes, DEV)
+    out = {}
+    for mode in ("eager", "per_subvolume", "graph"):
+        acc = torch.full((plan.total_active, 3), float("nan"), device=DEV)
+        mom = torch.empty((plan.B, 3), dtype=torch.float64, device=DEV)
+        plan.run(to_dev(b.pos), to_dev(b.mass), ws, acc, mom, mode)
+        torch.cuda.synchronize()
+        out[mode] = acc.cpu().numpy()
+        if mode != "per_subvolume":
+            assert int(ws[4 * 518:4 * 519].view(torch.int32).item()) == on
+    assert (plan.info()["sym_blocks"], plan.info()["sym_window"]) == tile
+    for mode in ("per_subvolume", "graph"):
+        assert np.array_equal(out["eager"].view(np.uint32), out[mode].view(np.uint32)), mode
+    p = b.part(0)
+    idx = synth.sample_indices(p.n, 2000, 1)
+    ref, _ = oracle.force(p.pos, p.mass, p.n_active, p.problem, targets=idx)
+    assert_force_close(out["graph"][idx], ref, what="first subvolume")
+    plan.close()
