@@ -496,7 +496,7 @@ sr_status sr_sparse_group(int group, int *cur /*host out*/);
 
 /* Host only.  How well the symmetric tiles have to spread.  Items are as large
  * as the tile configuration allows while their work (tile steps of all items)
- * spread over the persistent grid's waves is at least 5 min_ratio times the
+ * spread over the default launch's waves is at least 5 min_ratio times the
  * longest item, and smaller otherwise, so that a few long items cannot leave
  * most waves idle; the tiles are off only when the smallest items' work does
  * not even give four waves per compute unit min_ratio times the longest one (a

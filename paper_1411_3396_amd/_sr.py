@@ -681,7 +681,7 @@ def sparse_group(group: int = -1) -> int:
 
 def tile_balance(min_ratio: float = -1.0) -> float:
     """Set and return the balance rule of the symmetric tiles: their items are cut smaller while
-    the work per wave of the persistent grid is below 5 min_ratio longest items, and the tiles are
+    the work per wave of the default launch is below 5 min_ratio longest items, and the tiles are
     off when the smallest items' work gives four waves per compute unit less than min_ratio longest
     ones, a sixteenth of it for items of at most 1,024 tile steps (0: the configured items whenever
     the partial slots fit; -1 keeps the value)."""

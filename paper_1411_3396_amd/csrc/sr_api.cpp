@@ -251,7 +251,8 @@ sr_status check_ws(const void *ws, size_t ws_bytes, const Layout &L)
 // forward kernel (and the pair count), [1] the adjoint.  Defaults are the
 // fastest settings measured on the node-share workload.
 constexpr int kCfgForce = 0, kCfgVjp = 1;
-std::atomic<int> g_waves_default[2] = {{32}, {24}};
+constexpr int kWavesPerCu[2] = {32, 24};
+std::atomic<int> g_waves_default[2] = {{kWavesPerCu[0]}, {kWavesPerCu[1]}};
 std::atomic<int> g_tpl_default[2] = {{1}, {2}};
 std::atomic<int> g_occ_default[2] = {{6}, {0}};
 // Symmetric tiles of the dense cells, per kernel: blocks of 64 targets per
@@ -351,6 +352,7 @@ sr_status device_args(DevArgs &a, void *ws, const Layout *L, const SegParams *se
     a.st = static_cast<hipStream_t>(stream);
     a.waves_per_cu = waves_per_cu > 0 ? waves_per_cu : g_waves_default[cfg].load();
     a.num_cu = cus;
+    a.shape_waves_per_cu = kWavesPerCu[cfg];
     a.n_rows = (int)n_rows;
     a.targets_per_lane = g_tpl_default[cfg].load();
     a.occupancy = g_occ_default[cfg].load();

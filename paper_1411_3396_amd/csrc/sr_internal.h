@@ -144,6 +144,7 @@ struct DevArgs {
     hipStream_t st;
     int waves_per_cu;
     int num_cu;
+    int shape_waves_per_cu;  // waves per CU that the symmetric items' shape is chosen for, whatever the launch's
     int n_rows;  // rows of the force output (sum of n_active)
     int targets_per_lane;  // 1 or 2 for cells with more than 64 targets
     int occupancy;         // register-allocation hint of the pair kernels: 0, 6 or 8 waves/SIMD

@@ -1484,7 +1484,7 @@ __device__ __forceinline__ void full_dir(int f, int &dx, int &dy, int &dz)
 // there is little work.  k_sym_plan adds up, for each shape of a list from the
 // configured one (K, R) to finer ones, the partial slots and the longest item;
 // its last workgroup takes the first shape whose work per wave of the
-// persistent grid is at least kSymSpread balance longest items, else the
+// default persistent grid is at least kSymSpread balance longest items, else the
 // finest one whose work still gives four waves per CU balance longest items
 // (an item that short costs less alone on its SIMD than the one-sided items,
 // of 64 targets against every source, would), in both cases among those whose
@@ -2845,21 +2845,27 @@ bool all_softened(const DevArgs &a)
     return a.seg_host->pc.softened != 0;
 }
 
-unsigned persistent_grid(const DevArgs &a)
+// Waves of the persistent kernels at `per_cu` a compute unit: no more than a
+// list can hold items.
+unsigned waves_at(const DevArgs &a, int per_cu)
 {
-    int64_t g = (int64_t)a.num_cu * a.waves_per_cu;
-    if (g > a.L->item_cap) g = a.L->item_cap;
-    if (g < 1) g = 1;
-    return (unsigned)g;
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)a.num_cu * per_cu, a.L->item_cap));
 }
 
-// Waves of the symmetric kernels, and those the finest shape has to keep busy.
-int sym_waves(const DevArgs &a)
+unsigned persistent_grid(const DevArgs &a) { return waves_at(a, a.waves_per_cu); }
+
+// Waves of the symmetric kernels.
+int sym_waves(const DevArgs &a) { return (int)std::min<int64_t>(persistent_grid(a), a.L->sym_item_cap); }
+
+// Waves the symmetric items' shape is chosen for, and those its finest has to
+// keep busy: of the default launch, since the shape decides the order of sums
+// and launch settings must not.
+int shape_waves(const DevArgs &a)
 {
-    return (int)std::min<int64_t>(persistent_grid(a), a.L->sym_item_cap);
+    return (int)std::min<int64_t>(waves_at(a, a.shape_waves_per_cu), a.L->sym_item_cap);
 }
 
-int sym_few(const DevArgs &a) { return std::min(sym_waves(a), 4 * a.num_cu); }
+int sym_few(const DevArgs &a) { return std::min(shape_waves(a), 4 * a.num_cu); }
 
 // Whether the symmetric tiles can run at all: work over longest item is at
 // most the sum over cells of blocks times max(1, sources / W) (k_sym_plan), so
@@ -2897,7 +2903,7 @@ hipError_t plan_tiles(const DevArgs &a, Acc acc)
     }
     k_sym_plan<<<std::min(blocks_for(L.NC, 256), kListBlocks), 256, 0, a.st>>>(
         acc, (int)L.NC, at<int>(a, L.start), at<int>(a, L.nact), sh, at<uint32_t>(a, L.hdr), L.magic(),
-        (unsigned long long)L.sym_cap, sym_waves(a), sym_few(a), a.sym_balance, a.sym_gate);
+        (unsigned long long)L.sym_cap, shape_waves(a), sym_few(a), a.sym_balance, a.sym_gate);
     return hipGetLastError();
 }
 

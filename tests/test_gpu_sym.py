@@ -234,3 +234,28 @@ def test_short_items_of_little_work(n, side, halo_frac, on):
     assert oracle.rms_rel(gr, oracle.vjp(w.pos, w.mass, w.n_active, w.problem, g)) <= VJP_TOL
     a0, g0, _, _ = run(w, g, (0, -1))
     assert oracle.rms_rel(a, a0) <= 2e-6 and oracle.rms_rel(gr, g0) <= 2e-5
+
+
+@pytest.mark.parametrize("n,side,halo_frac,masses", [(60000, 36.0, 0.8, (1e3, 1e4)), (150000, 40.0, 0.5, (1e2, 1e4)),
+                                                     (12000, 20.0, 0.5, (1e3, 2e3))])
+def test_waves_per_cu_leaves_the_item_shape(n, side, halo_frac, masses):
+    # launch settings change no result: the shape of the symmetric items, and with it the
+    # order of sums, must not follow the number of waves they are launched with
+    w = synth.clustered_box(n, side, 30, 21, halo_frac=halo_frac, mass_range=masses)
+    w.mass = np.random.default_rng(4).uniform(0.5, 2.0, w.n).astype(np.float32)
+    g = synth.cotangent(w.n_active, 8)
+    a0, g0, f0, v0 = run(w, g, balance=1.0)
+    assert f0 == 1 and v0 == 1
+    saved = {k: sr.launch_config(kernel=k) for k in ("force", "vjp")}
+    try:
+        for waves in (1, 6, 12, 64):
+            announce(f"waves per CU {waves} n={w.n}")
+            for k in saved:
+                sr.launch_config(waves_per_cu=waves, kernel=k)
+            a, gr, f, v = run(w, g, balance=1.0)
+            assert (f, v) == (f0, v0), waves
+            assert np.array_equal(a.view(np.uint32), a0.view(np.uint32)), waves
+            assert np.array_equal(gr.view(np.uint32), g0.view(np.uint32)), waves
+    finally:
+        for k, v in saved.items():
+            sr.launch_config(*v, kernel=k)
