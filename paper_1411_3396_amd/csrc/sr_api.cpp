@@ -698,7 +698,10 @@ sr_status tune(sr_batch_plan *P, const float *pos, const float *mass, void *ws, 
     double best = 1e300;
     Cand pick{g_waves_default[kCfgForce].load(), 1, 0};
     P->sym_blocks = -1;
-    P->sym_window = -1;
+    // where the default windows put both kinds of items into one launch, half of
+    // these candidates would be the same kernel, and the others' hint would be
+    // picked by noise: windows of 512, whose kernels take it
+    P->sym_window = force_in_one_launch(g_sym_window[kCfgForce].load(), P->L.N) ? 512 : -1;
     P->sparse_group = -1;
     for (const Cand &c : cand) {
         P->waves_per_cu = c.w;
