@@ -554,46 +554,68 @@ namespace {
 // size.  Slots cost 16 B of traffic per 8 B superblock entry against B pair
 // steps, so B is 512 or more where that leaves several items per wave (a
 // superblock of 1024 from 3e10 ordered pairs on, where it still gives 14,000),
-// 256 where the catalogue is small; then it doubles (to 4096 at most, items of
-// a few ms) while the rows do not fit kSlotBytes, and what still does not fit
-// takes the smaller halos back to the one-sided items.
+// 256 where the catalogue is small; then it doubles (to kSymMaxBlock at most,
+// items of a few ms) while the rows do not fit kSlotBytes, and what still does
+// not fit takes the smaller halos back to the one-sided items.  A halo whose
+// rows alone do not fit (more than 737,460 particles) is one-sided from the
+// start, so that it does not decide the others' B.  Beside such a halo the
+// others go pair-once only if that is clearly shorter, by a count of the time
+// of both ways: its items of 128 targets against every source last long and
+// leave waves idle (7,565 of 8,192 for 968,359 particles, 208 ms), which the
+// others' one-sided items fill, whereas their pair-once items, at 0.7 of the
+// time a pair, come before and have a tail of their own.  One-sided against
+// pair-once, by the count's ratio: 968,359 with 300 of 20,000 particles 224 /
+// 226 ms (1.04), with 30 of 100,000 254 / 259 (0.99), two of 800,000 with 400 of
+// 30,000 325 / 328 (0.93), the node catalogue (968,359 the largest of 1,923)
+// 347 / 328 ms (0.91).
 constexpr double kSlotBytes = 1073741824.0;
+constexpr int kSymMaxBlock = 4096;
+constexpr double kSymPairTime = 0.7;
+constexpr double kSymClear = 0.92;
+constexpr double kOneSidedWaves = 8192.0;  // 32 per CU
 
 std::vector<int> pair_once_halos(int n_halos, const int64_t *offsets, int &block)
 {
+    const auto rows = [&](int h, int B) { return (double)((offsets[h + 1] - offsets[h] + B - 1) / B); };
+    const auto bytes = [&](int h, int B) { return 8.0 * (double)(offsets[h + 1] - offsets[h]) * (rows(h, B) + 1.0); };
     std::vector<int> sym;
-    double pairs = 0.0;
+    double pairs = 0.0, all_pairs = 0.0, longest = 0.0;  // longest: the items of halos that do not fit
     for (int h = 0; h < n_halos; ++h) {
-        const int64_t nh = offsets[h + 1] - offsets[h];
+        const double nh = (double)(offsets[h + 1] - offsets[h]);
+        all_pairs += nh * nh;
         if (nh <= kSymMin) continue;
+        if (bytes(h, kSymMaxBlock) > kSlotBytes) {
+            longest = std::max(longest, 2.0 * kTargetsPerWave * nh);
+            continue;
+        }
         sym.push_back(h);
-        pairs += (double)nh * (double)nh;
+        pairs += nh * nh;
     }
     std::stable_sort(sym.begin(), sym.end(), [&](int a, int b) {
         return offsets[a + 1] - offsets[a] > offsets[b + 1] - offsets[b];
     });
-    auto rows = [&](int h) {
-        const int64_t nh = offsets[h + 1] - offsets[h];
-        return (nh + block - 1) / block;
-    };
-    auto bytes = [&]() {
+    const auto all_bytes = [&](int B) {
         double b = 0.0;
-        for (const int h : sym) b += 8.0 * (double)(offsets[h + 1] - offsets[h]) * (double)(rows(h) + 1);
+        for (const int h : sym) b += bytes(h, B);
         return b;
     };
     block = pairs >= 3.0e10 ? 1024 : (pairs >= 4.0e9 ? 512 : 256);
-    while (block < 4096 && bytes() > kSlotBytes) block *= 2;
+    while (block < kSymMaxBlock && all_bytes(block) > kSlotBytes) block *= 2;
     // halos that fit, and items that fit 32-bit counters
-    double used = 0.0, items = 0.0;
+    double used = 0.0, items = 0.0, once = 0.0;
     std::vector<int> fit;
     for (const int h : sym) {
-        const double r = (double)rows(h), b = 8.0 * (double)(offsets[h + 1] - offsets[h]) * (r + 1.0);
+        const double r = rows(h, block), b = bytes(h, block);
         const double it = r * (r + 1.0) / 2.0;
         if (used + b > kSlotBytes || items + it > 1.0e9) continue;
         used += b;
         items += it;
+        once += (double)(offsets[h + 1] - offsets[h]) * (double)(offsets[h + 1] - offsets[h]);
         fit.push_back(h);
     }
+    const auto one_sided = [&](double p) { return std::max(p / kOneSidedWaves, longest); };
+    const double split = one_sided(all_pairs - once) + kSymPairTime * once / kOneSidedWaves;
+    if (longest > 0.0 && split > kSymClear * one_sided(all_pairs)) fit.clear();
     return fit;
 }
 

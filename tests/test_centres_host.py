@@ -59,3 +59,18 @@ def test_item_slots_fit_their_bits():
     if code == 0:
         _sr.lib().sr_centres_plan_destroy(plan)
     assert code == 5
+
+
+def test_pair_once_beside_a_halo_too_large_for_it():
+    # a halo whose rows alone exceed 1 GiB of slots is summed from both ends and leaves waves
+    # idle; a few others fill them from both ends too (no slots), many go pair-once
+    def need(sizes):
+        code, plan, nbytes = _create(np.concatenate([[0], np.cumsum(sizes)]))
+        assert code == 0
+        _sr.lib().sr_centres_plan_destroy(plan)
+        return nbytes
+
+    assert need([737460]) > 1000 << 20 and need([737461]) < 1 << 20
+    assert need([4000] * 50) > 50 * 8 * 4000 * 17
+    assert need([968359] + [4000] * 50) < 1 << 20
+    assert need([968359] + [270000] * 7 + [100000] * 35) > 7 * 8 * 270000 * 67
