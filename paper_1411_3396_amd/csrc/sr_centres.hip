@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64, 4) void k_centre_potential(
 // cut along both axes, where an item of 128 targets walked all its sources.
 // 2,000 halos of 40 to 86,000 particles (1.65e10 ordered pairs): 7.1 -> 2.5 ms
 // a run, 6.7e12 ordered pairs per second (2.3e12 before).
-constexpr int kSymMin = 256;    // halos above this many particles
+constexpr int kSymMin = 256;    // halos above this many particles (one superblock), where it pays: see pair_once_pays
 constexpr int kSymWin = 512;    // sources per window: 4 KB of float64 sums
 constexpr int kSymBlock = 2 * kWave;
 constexpr int kSumThreads = 256;
@@ -551,10 +551,13 @@ struct sr_centres_plan {
 namespace {
 
 // The halos that evaluate every pair once, largest first, and their superblock
-// size.  Slots cost 16 B of traffic per 8 B superblock entry against B pair
-// steps, so B is 512 or more where that leaves several items per wave (a
-// superblock of 1024 from 3e10 ordered pairs on, where it still gives 14,000),
-// 256 where the catalogue is small; then it doubles (to kSymMaxBlock at most,
+// size.  A smaller B cuts more items and keeps more slots, 8 B per particle and
+// partner superblock, so B rises where the slots of 256 would be some 128 MB
+// (4e9 ordered pairs) and those of 512 some 500 MB (3e10): each step halves
+// them and costs up to a sixth of the time at its line, nothing well above it
+// (256 / 512 / 1024, ms: 10 halos of 20,000 particles 0.60 / 0.67 / 0.95, 50 2.61
+// / 2.64 / 3.2, 75 3.87 / 3.85 / 4.47, 150 7.49 / 7.49 / 8.0; one of 170,000 3.68 /
+// 3.62 / 3.90, of 300,000 11.2 each).  Then it doubles (to kSymMaxBlock at most,
 // items of a few ms) while the rows do not fit kSlotBytes, and what still does
 // not fit takes the smaller halos back to the one-sided items.  A halo whose
 // rows alone do not fit (more than 737,460 particles) is one-sided from the
@@ -573,6 +576,50 @@ constexpr int kSymMaxBlock = 4096;
 constexpr double kSymPairTime = 0.7;
 constexpr double kSymClear = 0.92;
 constexpr double kOneSidedWaves = 8192.0;  // 32 per CU
+
+// Whether the pair-once items of `fit` are worth their two launches in a
+// catalogue whose one-sided items (at most one per wave) would be few: a count
+// of the microseconds of both ways.  One-sided: the longest item, 47 ns a source
+// while few waves share a SIMD, and the queue and the pairs of all items.
+// Pair-once: two launches and the longest item of 256 targets and sources, some
+// 35 us, the items beyond the first 1,280, and the halos of up to kSymMin in a
+// launch of their own.  One-sided against pair-once, us: 300 halos of 20 to 300
+// particles 31 / 54, of 20 to 2,000 192 / 119; 100 of 500 40 / 48, 500 of 500
+// 90 / 63; one of 600 39 / 42, one of 800 48 / 42.  On 93 such catalogues the
+// count takes the slower way by more than 2% once (600 halos of 20 to 700, 86 /
+// 92).
+bool pair_once_pays(int n_halos, const int64_t *offsets, const std::vector<int> &fit, int block)
+{
+    constexpr double kSource = 0.047, kItem = 0.015, kItemSource = 2.1e-5, kTwoLaunches = 35.0, kOnceItem = 0.02,
+                     kOnceFree = 1280.0, kLaunch = 6.0;
+    struct Cost {
+        double longest = 0.0, items = 0.0, time = 0.0;
+        void add(double n)
+        {
+            const double k = std::ceil(n / (2 * kTargetsPerWave));
+            longest = std::max(longest, n);
+            items += k;
+            time += k * (kItem + kItemSource * n);
+        }
+        double us() const { return kSource * longest + time; }
+    } all, rest;
+    std::vector<char> once(n_halos, 0);
+    double sym = 0.0;
+    for (const int h : fit) {
+        const double r = std::ceil((double)(offsets[h + 1] - offsets[h]) / block);
+        once[h] = 1;
+        sym += r * (r + 1.0) / 2.0;
+    }
+    for (int h = 0; h < n_halos; ++h) {
+        const double n = (double)(offsets[h + 1] - offsets[h]);
+        all.add(n);
+        if (!once[h]) rest.add(n);
+    }
+    if (all.items > kOneSidedWaves) return true;
+    const double split = kTwoLaunches + kOnceItem * std::max(0.0, sym - kOnceFree) +
+                         (rest.items > 0.0 ? kLaunch + rest.us() : 0.0);
+    return split < all.us();
+}
 
 std::vector<int> pair_once_halos(int n_halos, const int64_t *offsets, int &block)
 {
@@ -616,6 +663,7 @@ std::vector<int> pair_once_halos(int n_halos, const int64_t *offsets, int &block
     const auto one_sided = [&](double p) { return std::max(p / kOneSidedWaves, longest); };
     const double split = one_sided(all_pairs - once) + kSymPairTime * once / kOneSidedWaves;
     if (longest > 0.0 && split > kSymClear * one_sided(all_pairs)) fit.clear();
+    if (!fit.empty() && !pair_once_pays(n_halos, offsets, fit, block)) fit.clear();
     return fit;
 }
 

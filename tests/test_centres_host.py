@@ -61,16 +61,27 @@ def test_item_slots_fit_their_bits():
     assert code == 5
 
 
+def _need(sizes):
+    code, plan, nbytes = _create(np.concatenate([[0], np.cumsum(sizes)]))
+    assert code == 0
+    _sr.lib().sr_centres_plan_destroy(plan)
+    return nbytes
+
+
+def test_pair_once_of_small_catalogues():
+    # a few small halos do not pay for the pair-once launches (no slots), many or larger ones do
+    slots = lambda k, n: k * 8 * n * ((n + 255) // 256 + 1)  # noqa: E731
+    for k, n, once in ((1, 300, 0), (100, 400, 0), (100, 500, 0), (1, 600, 0), (1, 800, 1), (500, 300, 1), (100, 700, 1),
+                       (2000, 300, 1)):
+        assert (_need([n] * k) >= slots(k, n)) == bool(once), (k, n)
+    assert _need([100] * 300 + [700] * 3) < 40000 < slots(3, 700)
+    assert _need([100] * 300 + [2000]) >= slots(1, 2000)
+
+
 def test_pair_once_beside_a_halo_too_large_for_it():
     # a halo whose rows alone exceed 1 GiB of slots is summed from both ends and leaves waves
     # idle; a few others fill them from both ends too (no slots), many go pair-once
-    def need(sizes):
-        code, plan, nbytes = _create(np.concatenate([[0], np.cumsum(sizes)]))
-        assert code == 0
-        _sr.lib().sr_centres_plan_destroy(plan)
-        return nbytes
-
-    assert need([737460]) > 1000 << 20 and need([737461]) < 1 << 20
-    assert need([4000] * 50) > 50 * 8 * 4000 * 17
-    assert need([968359] + [4000] * 50) < 1 << 20
-    assert need([968359] + [270000] * 7 + [100000] * 35) > 7 * 8 * 270000 * 67
+    assert _need([737460]) > 1000 << 20 and _need([737461]) < 1 << 20
+    assert _need([4000] * 50) > 50 * 8 * 4000 * 17
+    assert _need([968359] + [4000] * 50) < 1 << 20
+    assert _need([968359] + [270000] * 7 + [100000] * 35) > 7 * 8 * 270000 * 67
