@@ -652,13 +652,16 @@ void cache_store(const std::string &path, const std::string &key, int waves, int
     std::rename(tmp.c_str(), path.c_str());
 }
 
-// Pick the launch parameters (persistent grid in waves per CU, targets per
-// lane of dense items, register-allocation variant) by timing the batched
-// sequence, then the tiles of the symmetric kernel (blocks per item, window,
-// or off), then the targets per item of sparse cells, each stage with the
-// choices before it.  Launch parameters do not change results; the tiles and
-// the sparse groups change only the order of the float32 sums (and so the
-// last bits), and are fixed once the plan is tuned.
+// Pick the tiles of the symmetric kernel (blocks per item, window, or off),
+// then the targets per item of sparse cells, then the launch parameters
+// (persistent grid in waves per CU, targets per lane of dense items,
+// register-allocation variant) by timing the batched sequence, each stage with
+// the choices before it.  The launch comes last, so that it is timed on the
+// kernels that will run: before the tiles, a batch of at most 2^18 particles
+// would time the kernel of both kinds of items, which has no register hint.
+// Launch parameters do not change results; the tiles and the sparse groups
+// change only the order of the float32 sums (and so the last bits), and are
+// fixed once the plan is tuned.
 sr_status tune(sr_batch_plan *P, const float *pos, const float *mass, void *ws, float *acc,
                hipStream_t st)
 {
@@ -690,34 +693,10 @@ sr_status tune(sr_batch_plan *P, const float *pos, const float *mass, void *ws, 
         ms_out = ms;
         return SR_OK;
     };
-    struct Cand {
-        int w, t, o;
-    };
-    const Cand cand[] = {{16, 1, 0}, {32, 1, 0}, {16, 2, 0}, {32, 2, 0}, {24, 1, 6},
-                         {32, 1, 6}, {24, 2, 6}, {32, 2, 6}, {32, 1, 8}, {32, 2, 8}};
-    double best = 1e300;
-    Cand pick{g_waves_default[kCfgForce].load(), 1, 0};
-    P->sym_blocks = -1;
-    // where the default windows put both kinds of items into one launch, half of
-    // these candidates would be the same kernel, and the others' hint would be
-    // picked by noise: windows of 512, whose kernels take it
-    P->sym_window = force_in_one_launch(g_sym_window[kCfgForce].load(), P->L.N) ? 512 : -1;
+    P->waves_per_cu = g_waves_default[kCfgForce].load();
+    P->targets_per_lane = 1;
+    P->occupancy = g_occ_default[kCfgForce].load();
     P->sparse_group = -1;
-    for (const Cand &c : cand) {
-        P->waves_per_cu = c.w;
-        P->targets_per_lane = c.t;
-        P->occupancy = c.o;
-        double ms = 0;
-        const sr_status s = time_runs(ms);
-        if (s != SR_OK) return s;
-        if (ms < best) {
-            best = ms;
-            pick = c;
-        }
-    }
-    P->waves_per_cu = pick.w;
-    P->targets_per_lane = pick.t;
-    P->occupancy = pick.o;
     struct Tile {
         int k, w;
     };
@@ -750,9 +729,31 @@ sr_status tune(sr_batch_plan *P, const float *pos, const float *mass, void *ws, 
             gpick = gsz;
         }
     }
+    P->sparse_group = gpick;
+    struct Cand {
+        int w, t, o;
+    };
+    const Cand cand[] = {{16, 1, 0}, {32, 1, 0}, {16, 2, 0}, {32, 2, 0}, {24, 1, 6},
+                         {32, 1, 6}, {24, 2, 6}, {32, 2, 6}, {32, 1, 8}, {32, 2, 8}};
+    double best = 1e300;
+    Cand pick{P->waves_per_cu, P->targets_per_lane, P->occupancy};
+    for (const Cand &c : cand) {
+        P->waves_per_cu = c.w;
+        P->targets_per_lane = c.t;
+        P->occupancy = c.o;
+        double ms = 0;
+        const sr_status s = time_runs(ms);
+        if (s != SR_OK) return s;
+        if (ms < best) {
+            best = ms;
+            pick = c;
+        }
+    }
+    P->waves_per_cu = pick.w;
+    P->targets_per_lane = pick.t;
+    P->occupancy = pick.o;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    P->sparse_group = gpick;
     P->tuned_ms = std::min(best, std::min(best_t, best_g)) / 2.0;
     cache_store(P->tune_cache, P->tune_key, pick.w, pick.t, pick.o, tpick.k, tpick.w, gpick, P->tuned_ms);
     return SR_OK;

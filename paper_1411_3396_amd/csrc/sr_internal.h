@@ -134,11 +134,6 @@ struct Layout {
 // Sizes of the scan scratch for an array of m elements.
 int64_t scan_scratch_elems(int64_t m);
 
-// Whether a forward pass takes one-sided and symmetric items in one launch (where the
-// tiles can run at all); that kernel has no register-allocation hint.
-constexpr int64_t kBothForce = int64_t(1) << 18;
-inline bool force_in_one_launch(int window, int64_t N) { return window == 256 && N <= kBothForce; }
-
 // Device-path entry points implemented in sr_kernels.hip.  All enqueue on
 // `st` and return hipSuccess or the first launch error.
 struct DevArgs {

@@ -3107,7 +3107,8 @@ void launch_vjp_sym(const DevArgs &a, Acc acc)
 // uniform 2 million 0.92 -> 0.935); in the forward the one-sided items lose two
 // of their seven waves per SIMD to the tiles' registers (uniform 2 million 0.66
 // -> 0.73 ms), which from some 300,000 particles on costs more than the tails.
-bool force_both(const DevArgs &a) { return force_in_one_launch(a.sym_window, a.L->N); }
+constexpr int64_t kBothForce = int64_t(1) << 18;
+bool force_both(const DevArgs &a) { return a.sym_window == 256 && a.L->N <= kBothForce; }
 bool vjp_both(const DevArgs &a) { return a.sym_window == 256; }
 
 template <class Acc, bool kSoft>
