@@ -208,14 +208,14 @@ sr_status sr_force_vjp(const float *pos, const float *mass, int64_t n, int64_t n
 /* Forward without any device allocation, for callers that cannot allocate:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Computes what sr_force computes without SR_REUSE_BINS (bin,
- * then the forward pair kernels; the same kernels, so bitwise the same
- * accelerations), but its workspace is a fixed device array of
- * SR_STATIC_WORKSPACE_BYTES inside the library, one per GPU, held until the
+ * then the forward pair kernels; the same kernels, so bitwise the accelerations
+ * of sr_force with a workspace of that size), but its workspace is a fixed device
+ * array of SR_STATIC_WORKSPACE_BYTES inside the library, one per GPU, held until the
  * process ends.  The caller passes only inputs and outputs: pos [n][3], mass
  * [n] (device, read only), acc [n_active][3] (device, overwritten).
  * Returns SR_E_UNSUPPORTED, before touching the device, when the problem
  * needs a larger workspace than that (sr_workspace_bytes gives the need:
- * some 270 B per particle plus 180 B per cell at least); SR_E_DEVICE if the array's
+ * some 270 B per particle plus 224 B per cell at least); SR_E_DEVICE if the array's
  * address cannot be looked up; other errors as sr_force.  Never calls
  * hipMalloc or hipFree.  Every call on one GPU shares that GPU's array and
  * leaves its contents there (each call re-initialises what it reads), so

@@ -370,9 +370,9 @@ sr_status device_args(DevArgs &a, void *ws, const Layout *L, const SegParams *se
 
 // Most targets per sparse item of one problem: the configured value, but for the
 // default the smallest the item list is sized for while the targets make at most
-// kSpreadItems full items: these and the parts of items fit the persistent
-// grid's waves (8,192) once, so every wave has at most one item, with more lanes
-// per target.  A step of 4,000 / 12,000 / 32,768 uniform particles 133 / 138 / 146
+// kSpreadItems full items: these and the parts of items, about one a cell, fit
+// the persistent grid's waves (8,192; the adjoint's 6,144) once, so every wave has
+// at most one item, with more lanes per target.  A step of 4,000 / 12,000 / 32,768 uniform particles 133 / 138 / 146
 // -> 121 / 120 / 136 us, a force of 1,000 59 -> 53 us; clustered ones within 1%.
 // With twice the items, 50,000 took 209 us instead of 163 (some waves have two);
 // groups of 4 measured 121 / 126 / 136 us.  The choice depends on the number of

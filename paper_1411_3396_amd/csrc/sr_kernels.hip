@@ -286,6 +286,10 @@ __global__ __launch_bounds__(256) void k_scan_add(const int *__restrict__ in, in
 // Exclusive scan of in[0..m) into out[0..m] (out[m] = total).  tmp holds
 // scan_scratch_elems(m) ints.  A dependent launch costs some 4.5 us, so a
 // scan takes one launch up to kScanAlone blocks of 2048, two up to kScanSums.
+// Binning uniform particles with kScanAlone 0 / 16 / 128: 270,000 72 / 66 / 66 us,
+// 524,288 81 / 78 / 78, 1,000,000 98 / 98 / 114, 4,000,000 245 / 245 / 339; with
+// kScanSums 64 / 256 / 2048 / 16384: 4,000,000 252 / 246 / 245 / 245, 20,000,000
+// 1,250 / 1,250 / 1,241 / 1,240.
 hipError_t scan_i32(const int *in, int *out, int64_t m, int *tmp, hipStream_t st)
 {
     const int64_t nb = std::max<int64_t>(1, (m + kScanBlock - 1) / kScanBlock);
@@ -433,9 +437,11 @@ __global__ __launch_bounds__(256) void k_radix_hist(const int *__restrict__ keys
 // counts of every tile (tile by tile), which the workgroup adds up itself to
 // find where its digits start; otherwise their exclusive scan.
 //
-// kDirect serves sorts of at most kDirectTiles tiles: the scan's three
-// launches, some 4.5 us each, are most of such a sort, and 128 tiles are 128
-// loads per digit, all in flight.  It takes 16 waves a tile, since there are
+// kDirect serves sorts of at most kDirectTiles tiles: the scan's launches, some
+// 4.5 us each, are most of such a sort, and 128 tiles are 128 loads per digit,
+// all in flight.  Binning uniform particles, this way / with the scan: 30,000 31
+// / 38 us, 100,000 35 / 45, 262,144 (the line) 61 / 66, 270,000 64 / 66, 400,000
+// 77 / 72, 1,000,000 139 / 98.  It takes 16 waves a tile, since there are
 // fewer tiles than CUs and the ranking is a chain of kRadixTile / 64 / kWaves
 // steps.
 constexpr int kDirectTiles = 128;
@@ -2680,7 +2686,7 @@ __global__ __launch_bounds__(64, 1) void k_vjp_both(
 // slots per particle with eight loads in flight, instead of one run per
 // direction with its own bounds and division, took the pass on 16.8 million
 // clustered particles from 0.87 to 0.41 ms and on the node share from 2.23 to
-// 2.05 ms (4.2 TB/s).
+// 2.02 ms (6.9 GB, 3.4 TB/s).
 __global__ __launch_bounds__(256) void k_sym_gather(int N, int key_bits, const int *__restrict__ key,
                                                     const int *__restrict__ start,
                                                     const int *__restrict__ nact,
@@ -2867,9 +2873,16 @@ int shape_waves(const DevArgs &a)
 
 int sym_few(const DevArgs &a) { return std::min(shape_waves(a), 4 * a.num_cu); }
 
-// Whether the symmetric tiles can run at all: work over longest item is at
-// most the sum over cells of blocks times max(1, sources / W) (k_sym_plan), so
-// at most n / 64 max(1, n / W), and k_sym_plan asks for balance times few.
+// Whether the symmetric tiles can run at all.  Work over longest item is at most
+// the sum over cells of blocks times max(1, sources / W) (k_sym_plan), so at most
+// n / 64 max(1, n / W), and k_sym_plan asks for balance times few, or, of short
+// items, a kSymLone-th of it.  The line here is the former for both: the shape
+// decision and the gather cost a small call some 5 us each, and a list pass of
+// a lightly clustered one 10 more, which only a single halo of most of the
+// particles earns back.  With the latter, forces and adjoints in a box of 27
+// units: 2,500 uniform particles 49 -> 54 and 25 -> 30 us, half of them in six
+// halos 72 -> 91 and 78 -> 96, 70% of 3,500 in one halo 233 -> 100 and 442 -> 89.
+// At a grid of 1,024 waves or more the line is at 4,096 particles.
 bool sym_possible(const DevArgs &a)
 {
     const double n = (double)a.L->N;

@@ -366,3 +366,41 @@ def test_default_sparse_group_at_the_edge_of_its_rule(n):
         assert np.array_equal(a, a8) and np.array_equal(gr, g8)
     assert oracle.rms_rel(a, a8) <= 2e-6
     assert oracle.rms_rel(gr, g8) <= 2e-5
+
+
+@pytest.mark.parametrize("n,eight", [(32768, True), (32769, False)])
+def test_default_sparse_group_on_either_side_of_its_line(n, eight):
+    # cells of some 27 to 33 particles: items of 8 and of 16 targets give each target other
+    # numbers of lanes, so the bits tell which of the two the default took
+    w = synth.uniform_box(n, 32.0, 73)
+    g = synth.cotangent(w.n_active, 14)
+    announce(f"sparse group line n={n}")
+    saved = sr.sparse_group()
+    try:
+        sr.sparse_group(16)
+        a, gr = gpu_force(w), gpu_vjp(w, g)
+        sr.sparse_group(8)
+        a8, g8 = gpu_force(w), gpu_vjp(w, g)
+    finally:
+        sr.sparse_group(saved)
+    assert np.array_equal(a, a8) == eight and np.array_equal(gr, g8) == eight
+
+
+@pytest.mark.parametrize("sizes", [[100] * 40, [2900, 1500, 700]])
+def test_persistent_loop_bound_of_each_centre_kernel(monkeypatch, sizes):
+    # one catalogue of one-sided halos only and one of pair-once halos only: each kernel's
+    # own loop bound flags the workspace
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    pos = to_dev(np.random.default_rng(4).normal(size=(off[-1], 3)).astype(np.float32))
+    mass = torch.ones(int(off[-1]), device=DEV)
+    plan = sr.CentresPlan(off)
+    ws = sr.new_workspace(plan.ws_bytes, DEV)
+    announce(f"centre loop bound {len(sizes)} halos")
+    plan.run(pos, mass, 0.05, ws)
+    assert sr.ws_flags(ws) == 0
+    monkeypatch.setenv("SR_PULL_LIMIT", "0")
+    plan.run(pos, mass, 0.05, ws)
+    torch.cuda.synchronize()
+    monkeypatch.delenv("SR_PULL_LIMIT")
+    assert sr.ws_flags(ws) & sr._sr.FLAG_QUEUE
+    plan.close()
