@@ -369,9 +369,10 @@ sr_status sr_blocks_reconcile_grad(const sr_blocks_plan *plan, const void *ws, s
  * most 8, so the rounding does not grow with the halo size.  Halos of more
  * than 256 particles evaluate every pair once, its two terms kept in float64
  * partial sums in the workspace (8 B per particle and 256 to 4096 partners,
- * at most 1 GiB in all; a halo that alone needs more, from 737,461 particles
- * on, and the smaller halos once the largest fill it are summed from both
- * ends).  The most-bound choice is
+ * at most 1 GiB in all, taken from the largest halo on as each fits: a halo
+ * that alone needs more, from 737,461 particles on, and those that do not fit
+ * beside the ones taken are summed from both ends, and so is a catalogue where
+ * that is faster, such as a few halos of some hundred particles).  The most-bound choice is
  * made on the float32 phi that is returned.  Results do not depend on the
  * launch (every sum has a fixed order). */
 typedef struct sr_centres_plan sr_centres_plan;
