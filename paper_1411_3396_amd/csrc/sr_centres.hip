@@ -559,8 +559,8 @@ namespace {
 // / 2.64 / 3.2, 75 3.87 / 3.85 / 4.47, 150 7.49 / 7.49 / 8.0; one of 170,000 3.68 /
 // 3.62 / 3.90, of 300,000 11.2 each).  Then it doubles (to kSymMaxBlock at most,
 // items of a few ms) while the rows do not fit kSlotBytes, and then the halos are
-// taken from the largest on as each fits; the others go to the one-sided items.  A halo whose
-// rows alone do not fit (more than 737,460 particles) is one-sided from the
+// taken from the largest on as each fits; the others go to the one-sided items.
+// A halo whose rows alone do not fit (more than 737,460 particles) is one-sided from the
 // start, so that it does not decide the others' B.  Beside such a halo the
 // others go pair-once only if that is clearly shorter, by a count of the time
 // of both ways: its items of 128 targets against every source last long and
